@@ -1,0 +1,212 @@
+"""GPU parity of the SF rebuild with operands split beforehand into fp16 parts
+(layers of at least two 128 x 128 tiles per CU and 4 GFLOP): the edges of its
+tiles, K groups and value ranges, and the scratch memory its streams keep."""
+import threading
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from _helpers import BUF_TOL, DELTA_TOL, W_TOL, assert_close, dev, log, sample_points, sf_arithmetic, to_np
+from paper_1706_03292_amd import api
+from paper_1706_03292_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+# K of 8, 9 and 10 groups of 16 rows (the ring of three stages ends in each of
+# its stages), whole and partial; M and N one past a tile, one short of one,
+# and with the tile's second panel outside the matrix.
+@pytest.mark.parametrize("M,N,K", [(4096, 4096, 128), (4097, 4160, 129), (4095, 4161, 144), (4224, 4033, 160),
+                                   (2049, 8200, 143)])
+@pytest.mark.parametrize("momentum", [False, True])
+def test_sf_half_edges(M, N, K, momentum):
+    d = dev()
+    W, U, V = I.randn(M + K, (M, N), 0.01), I.randn(M + K + 1, (K, M), 0.1), I.randn(M + K + 2, (K, N), 0.1)
+    buf = I.randn(M + K + 3, (M, N), 1e-3)
+    rows, cols = sample_points(M, N, 3000, seed=N)
+    log(f"sf half M={M} N={N} K={K} momentum={momentum}")
+    Wd, Ud, Vd = W.to(d), U.to(d), V.to(d)
+    if momentum:
+        bd = buf.to(d)
+        api.sf_apply_momentum(Wd, bd, Ud, Vd, 0.01, 0.9)
+        torch.cuda.synchronize()
+        w_ref, b_ref = oracle.sf_apply_momentum_points(W.numpy(), buf.numpy(), U.numpy(), V.numpy(), 0.01, 0.9, rows,
+                                                       cols)
+        assert_close(to_np(bd)[rows, cols], b_ref, BUF_TOL, "buf")
+    else:
+        api.sf_apply(Wd, Ud, Vd, 0.01)
+        torch.cuda.synchronize()
+        w_ref = oracle.sf_apply_points(W.numpy(), U.numpy(), V.numpy(), 0.01, rows, cols)
+        Z = torch.zeros(M, N, device=d)
+        api.sf_apply(Z, Ud, Vd, -1.0)
+        torch.cuda.synchronize()
+        ref = oracle.sf_apply_points(np.zeros((M, N), np.float32), U.numpy(), V.numpy(), -1.0, rows, cols)
+        assert_close(to_np(Z)[rows, cols], ref, DELTA_TOL, "raw gradient")
+    assert_close(to_np(Wd)[rows, cols], w_ref, W_TOL, "W")
+
+
+def _plant(kind, U, V):
+    """Values that leave the range of a panel's fp16 parts."""
+    K, M = U.shape
+    if kind == "tiny":               # below it: alone in their row of the gradient, and among others
+        U[:, 5] = 0
+        U[K - 1, 5] = 1e-12          # the partial last group
+        U[3, 200] = -3e-11
+        V[17, 70] = 2e-13
+        V[:, 4098] = 0
+        V[0, 4098] = 1e-20
+    elif kind == "subnormal":        # and below fp32's normal numbers
+        V[9, 9] = 1e-42
+    elif kind == "large":            # above it, in one panel
+        U[20, 130] = 3e7
+    elif kind == "zeros":            # whole panels and groups of zeros are in range
+        U[:, 64:128] = 0
+        V[16:32] = 0
+    elif kind == "scales":           # panels of very different size
+        U[:, 128:192] *= 2.0 ** 50
+        V[:, :64] *= 2.0 ** -45
+    elif kind == "extreme":          # panels beyond the exponents that are scaled at all
+        U[:, 0:64] *= 2.0 ** 90
+        V[:, 64:128] *= 2.0 ** -90
+    return U, V
+
+
+@pytest.mark.parametrize("kind", ["tiny", "subnormal", "large", "zeros", "scales", "extreme"])
+def test_sf_half_values_out_of_range_stay_fp32_grade(kind):
+    """Per element the raw gradient stays within 2 sqrt(K) + 16 units of 2^-24
+    of sum_k |U[k][m]| |V[k][n]| (fp32 rounding in any order of summation), also
+    where that sum consists of values far below the rest of their panel."""
+    d = dev()
+    M, N, K = 4133, 4099, 130
+    U, V = _plant(kind, I.randn(71, (K, M), 1.0), I.randn(72, (K, N), 1.0))
+    rows, cols = sample_points(M, N, 3000, seed=1)
+    rows = np.concatenate([rows, np.full(300, 5), np.full(300, 200), np.full(300, 130),
+                           np.arange(300), np.arange(300), np.arange(60, 360)])
+    cols = np.concatenate([cols, np.arange(300), np.arange(300), np.arange(300),
+                           np.full(300, 70), np.full(300, 4098), np.full(300, 9)])
+    Un, Vn = U.numpy().astype(np.float64), V.numpy().astype(np.float64)
+    ref = np.einsum("kp,kp->p", Un[:, rows], Vn[:, cols])
+    scale = np.einsum("kp,kp->p", np.abs(Un[:, rows]), np.abs(Vn[:, cols]))
+    units = {}
+    for arith in (api.SF_BF16X6, api.SF_FP32):
+        Z = torch.zeros(M, N, device=d)
+        log(f"sf half values {kind} arithmetic {arith}")
+        with sf_arithmetic(arith):
+            api.sf_apply(Z, U.to(d), V.to(d), -1.0)
+            torch.cuda.synchronize()
+        err = np.abs(to_np(Z)[rows, cols].astype(np.float64) - ref)
+        # (Results below fp32's normal numbers are rounded to its subnormal grid.)
+        units[arith] = np.max((err - 2.0 ** -126) / np.maximum(scale, 1e-300)) / 2.0 ** -24
+    assert units[api.SF_BF16X6] <= 2 * np.sqrt(K) + 16, units
+    assert units[api.SF_BF16X6] <= 2 * units[api.SF_FP32] + 4, units
+
+
+def test_sf_half_non_finite_operands():
+    """An infinite factor value makes its row of the gradient NaN, as with the
+    products of bf16 parts, and no other."""
+    d = dev()
+    M, N, K = 4133, 4099, 130
+    U, V = I.randn(81, (K, M), 1.0), I.randn(82, (K, N), 1.0)
+    U[40, 700] = float("inf")
+    Z = torch.zeros(M, N, device=d)
+    log("sf half infinite value")
+    api.sf_apply(Z, U.to(d), V.to(d), -1.0)
+    torch.cuda.synchronize()
+    assert bool(torch.isnan(Z[700]).all())
+    assert bool(torch.isfinite(Z[:700]).all()) and bool(torch.isfinite(Z[701:]).all())
+    cols = np.arange(0, N, 37)
+    rows = np.full(cols.size, 701)
+    ref = oracle.sf_apply_points(np.zeros((M, N), np.float32), np.nan_to_num(U.numpy(), posinf=0.0), V.numpy(), -1.0,
+                                 rows, cols)
+    assert_close(to_np(Z)[rows, cols], ref, DELTA_TOL, "a row beside it")
+
+
+def _layers(d, seed, shapes):
+    g = torch.Generator("cuda").manual_seed(seed)
+    rnd = lambda *s: torch.randn(*s, generator=g, device=d)   # noqa: E731
+    return [(rnd(M, N) * 0.01, rnd(K, M), rnd(K, N)) for M, N, K in shapes]
+
+
+def test_sf_half_scratch_of_streams_and_threads():
+    """Each stream's scratch is its own: layers rebuilt on two streams at once
+    from two threads, on one stream from two threads, and with growing and
+    shrinking operands end as one after the other."""
+    d = dev()
+    shapes = [(4096, 4096, 128), (4096, 8192, 200), (4096, 4096, 300)]
+    want = [_layers(d, 7 + t, shapes) for t in range(4)]
+    got = [[(W.clone(), U, V) for W, U, V in ls] for ls in want]
+    for ls in want:
+        for W, U, V in ls:
+            for _ in range(3):
+                api.sf_apply(W, U, V, 0.01)
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream(d), torch.cuda.Stream(d)]
+    failed = []
+
+    def work(t):
+        try:
+            for _ in range(3):
+                for W, U, V in got[t]:
+                    api.sf_apply(W, U, V, 0.01, stream=streams[t // 2])
+        except Exception as e:   # noqa: BLE001
+            failed.append(e)
+
+    log("sf half scratch, four threads on two streams")
+    threads = [threading.Thread(target=work, args=(t,)) for t in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    assert not failed, failed
+    for a, b in zip(want, got):
+        for (Wa, _, _), (Wb, _, _) in zip(a, b):
+            assert torch.equal(Wa, Wb)
+    # Destroying a pool gives the scratch back; the next rebuild finds some again.
+    api.StreamPool(1).close()
+    Z1, Z2 = torch.zeros(4096, 4096, device=d), torch.zeros(4096, 4096, device=d)
+    _, U, V = want[0][0]
+    api.sf_apply(Z1, U, V, -1.0)
+    with torch.cuda.stream(streams[0]):
+        api.sf_apply(Z2, U, V, -1.0)
+    torch.cuda.synchronize()
+    assert torch.equal(Z1, Z2)
+
+
+# Spread rebuilds beside longer applies: 64 x 64 and 128 x 128 tiles cut by the
+# matrix edges and a K that is no multiple of a slice, and the split operands'.
+@pytest.mark.parametrize("M,N,B,P,n,momentum", [(1000, 2048, 23, 12, 4_400_001, False),
+                                                (1000, 2048, 23, 12, 4_400_001, True),
+                                                (4100, 4000, 9, 4, 8_400_003, False),
+                                                (4096, 4096, 32, 8, 24_000_000, False),
+                                                (4100, 4033, 33, 8, 24_000_000, True)])
+def test_sync_iteration_spread_rebuild_equals_the_single_call(M, N, B, P, n, momentum):
+    d = dev()
+    K = B * P
+    g = torch.Generator("cuda").manual_seed(M + K)
+    rnd = lambda *s: torch.randn(*s, generator=g, device=d)   # noqa: E731
+    fc = {"fc": True, "W": rnd(M, N), "U": rnd(K, M), "V": rnd(K, N)}
+    if momentum:
+        fc["buf"] = rnd(M, N)
+    ps = {"fc": False, "W": rnd(n), "shards": rnd(P, n), "buf": rnd(n)}
+    want = {k: v.clone() for k, v in list(fc.items())[1:]}
+    pw, pb = ps["W"].clone(), ps["buf"].clone()
+    log(f"spread rebuild {M}x{N} K={K} beside {n} values at P={P}, momentum={momentum}")
+    pool = api.StreamPool(2)
+    pool.set_timing(True)
+    schemes = api.SyncIteration(pool, [fc, ps], B, P, 0.01, 0.9)()
+    assert schemes == [api.SFB, api.PS]
+    assert {r["stream"] for r in pool.launch_times()} == {0, 1}
+    if momentum:
+        api.sf_apply_momentum(want["W"], want["buf"], want["U"], want["V"], 0.01, 0.9)
+    else:
+        api.sf_apply(want["W"], want["U"], want["V"], 0.01)
+    api.ps_apply(pw, ps["shards"], 0.01, 0.9, pb)
+    torch.cuda.synchronize()
+    assert torch.equal(fc["W"], want["W"])
+    if momentum:
+        assert torch.equal(fc["buf"], want["buf"])
+    assert torch.equal(ps["W"], pw) and torch.equal(ps["buf"], pb)
+    pool.close()
