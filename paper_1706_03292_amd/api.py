@@ -8,6 +8,7 @@ rejected rather than handled.
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes
 
 import torch
@@ -43,10 +44,29 @@ def _dev_f32(name: str, t: torch.Tensor) -> torch.Tensor:
     return t
 
 
+# What a call asks of torch besides its arguments -- the current stream's raw
+# handle and the current device -- straight from the runtime's own accessors: a
+# torch.cuda.Stream object and a torch.cuda.device context per call took 2.5 of
+# the 5 us that a KV-store receive costs (sixteen of them and one apply: 84 us,
+# the apply alone 24).
+_raw_stream = torch._C._cuda_getCurrentRawStream
+_current_device = torch._C._cuda_getDevice
+_SAME_DEVICE = contextlib.nullcontext()
+
+
 def _stream_handle(stream, device) -> int:
     if stream is None:
+        if device.index is not None:
+            return _raw_stream(device.index)
         stream = torch.cuda.current_stream(device)
     return int(stream.cuda_stream) if hasattr(stream, "cuda_stream") else int(stream)
+
+
+def _on(device):
+    """torch.cuda.device(device), or nothing where that is current already."""
+    if device.index is not None and device.index == _current_device():
+        return _SAME_DEVICE
+    return torch.cuda.device(device)
 
 
 def _uses(stream, *tensors) -> None:
@@ -103,7 +123,7 @@ def sf_apply(W: torch.Tensor, U: torch.Tensor, V: torch.Tensor, lr: float, strea
     if U.shape != (K, M) or V.shape != (K, N):
         raise ValueError(f"shapes: W {tuple(W.shape)}, U {tuple(U.shape)}, V {tuple(V.shape)}")
     _uses(stream, W, U, V)
-    with torch.cuda.device(W.device):
+    with _on(W.device):
         _check("poseidon_sf_apply", L.lib().poseidon_sf_apply(
             W.data_ptr(), U.data_ptr(), V.data_ptr(), M, N, K, float(lr),
             _stream_handle(stream, W.device)))
@@ -123,7 +143,7 @@ def sf_apply_momentum(W: torch.Tensor, buf: torch.Tensor, U: torch.Tensor, V: to
         raise ValueError(f"shapes: W {tuple(W.shape)}, buf {tuple(buf.shape)}, U {tuple(U.shape)}, "
                          f"V {tuple(V.shape)}")
     _uses(stream, W, buf, U, V)
-    with torch.cuda.device(W.device):
+    with _on(W.device):
         _check("poseidon_sf_apply_momentum", L.lib().poseidon_sf_apply_momentum(
             W.data_ptr(), buf.data_ptr(), U.data_ptr(), V.data_ptr(), M, N, K, float(lr), float(momentum),
             _stream_handle(stream, W.device)))
@@ -164,7 +184,7 @@ def sf_apply_batch(layers: list, lr: float, stream=None) -> None:
             raise ValueError(f"layer {i}: U must be {K} x {M} and V {K} x {N}")
         arr[i] = L.PoseidonSfTensor(W.data_ptr(), U.data_ptr(), V.data_ptr(), M, N)
     _uses(stream, *[x for layer in layers for x in layer])
-    with torch.cuda.device(dev):
+    with _on(dev):
         _check("poseidon_sf_apply_batch", L.lib().poseidon_sf_apply_batch(
             arr, len(layers), K, float(lr), _stream_handle(stream, dev)))
 
@@ -183,7 +203,7 @@ def ps_apply(W: torch.Tensor, shards: torch.Tensor, lr: float, momentum: float =
     if shards.numel() != P * n or (buf is not None and buf.numel() != n):
         raise ValueError(f"shards must be P x {n} and buf must have {n} values")
     _uses(stream, W, shards, buf)
-    with torch.cuda.device(W.device):
+    with _on(W.device):
         _check("poseidon_ps_apply", L.lib().poseidon_ps_apply(
             W.data_ptr(), shards.data_ptr(), P, n, float(lr), float(momentum),
             buf.data_ptr() if buf is not None else None, _stream_handle(stream, W.device)))
@@ -216,7 +236,7 @@ def ps_apply_batch(tensors: list, lr: float, momentum: float = 0.0, stream=None)
             raise ValueError(f"tensor {i}: shards must be {P} x {n} and buf must have {n} values")
         arr[i] = L.PoseidonPsTensor(W.data_ptr(), shards.data_ptr(), buf.data_ptr() if buf is not None else None, n)
     _uses(stream, *[x for t in tensors for x in t])
-    with torch.cuda.device(dev):
+    with _on(dev):
         _check("poseidon_ps_apply_batch", L.lib().poseidon_ps_apply_batch(
             arr, len(tensors), P, float(lr), float(momentum), _stream_handle(stream, dev)))
 
@@ -282,7 +302,7 @@ class StreamPool:
         ``stream`` and ``ms``."""
         recs = (L.PoseidonLaunchRecord * capacity)()
         n = ctypes.c_int32()
-        with torch.cuda.device(self.device):
+        with _on(self.device):
             _check("poseidon_pool_launch_times",
                    L.lib().poseidon_pool_launch_times(self._h, recs, capacity, ctypes.byref(n)))
         return [{"scheme": r.scheme, "tensor": r.tensor, "stream": r.stream, "ms": r.ms} for r in recs[:n.value]]
@@ -362,7 +382,7 @@ class SyncIteration:
         # than the current one must be known to the caching allocator.
         if isinstance(stream, torch.cuda.Stream) and stream != torch.cuda.current_stream(self.pool.device):
             self._kept_uses(stream)
-        with torch.cuda.device(self.pool.device):
+        with _on(self.pool.device):
             if ready is None:
                 _check("poseidon_sync_iteration", L.lib().poseidon_sync_iteration(
                     self.pool.handle, self._arr, self.count, self.B, self.P, self.lr, self.momentum,
@@ -410,7 +430,7 @@ def kv_pack(grads: list, pair_elems: int, P: int, server: int, message: torch.Te
     ptrs = (ctypes.c_void_p * max(1, len(grads)))(*[g.data_ptr() for g in grads])
     n = ctypes.c_int64()
     h = _stream_handle(stream, dev)
-    with torch.cuda.device(dev):
+    with _on(dev):
         _check("poseidon_kv_pack", L.lib().poseidon_kv_pack(sizes, ptrs, len(grads), int(pair_elems), int(P),
                                                             int(server), None, 0, ctypes.byref(n), h))
         if message is None:
@@ -457,7 +477,7 @@ class KVStore:
         self.P, self.rank = int(P), int(rank)
         self._h = ctypes.c_void_p()
         self._grads = {}
-        with torch.cuda.device(self.device):
+        with _on(self.device):
             _check("poseidon_kv_create", L.lib().poseidon_kv_create(arr, len(tensors), int(pair_elems), self.P,
                                                                     self.rank, float(lr), float(momentum),
                                                                     ctypes.byref(self._h)))
@@ -476,7 +496,7 @@ class KVStore:
         if grad.device != self.device:
             raise ValueError("grad must be on the store's device")
         _uses(stream, grad)
-        with torch.cuda.device(self.device):
+        with _on(self.device):
             done = _check("poseidon_kv_receive", L.lib().poseidon_kv_receive(
                 self._h, int(worker), int(tensor), grad.data_ptr(), _stream_handle(stream, self.device)))
         sid = _stream_id(stream)
@@ -496,7 +516,7 @@ class KVStore:
         if message.device != self.device:
             raise ValueError("message must be on the store's device")
         _uses(stream, message)
-        with torch.cuda.device(self.device):
+        with _on(self.device):
             done = _check("poseidon_kv_receive_message", L.lib().poseidon_kv_receive_message(
                 self._h, int(worker), message.data_ptr() if message.numel() else None,
                 _stream_handle(stream, self.device)))
