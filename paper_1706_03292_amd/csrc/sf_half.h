@@ -380,15 +380,21 @@ __device__ __forceinline__ void sf_tile_half(float* __restrict__ W, const float*
     const __amdgpu_buffer_rsrc_t wr = tile_rsrc(W, M, N, m0 * N + n0);
     const int n4 = static_cast<int>(N) * 4;
     const int voff = ((wm + 4 * lrow) * static_cast<int>(N) + wn + lcol) * 4;
-    float wx[4][16];
-    auto load_w = [&](int c) {
+    // With a momentum buffer it is read ahead, else W.
+    const __amdgpu_buffer_rsrc_t xr = MOM ? tile_rsrc(buf, M, N, m0 * N + n0) : wr;
+    float ahead_v[4][16];
+    auto load_block = [&](float (&v)[16], __amdgpu_buffer_rsrc_t rs, int c) {
 #pragma unroll
         for (int r = 0; r < 16; ++r)
-            wx[c][r] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
-                                                     wr, voff + 128 * (c % 2), acc_row(c / 2, r) * n4, W_AUX));
+            v[r] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, voff + 128 * (c % 2),
+                                                                                acc_row(c / 2, r) * n4, W_AUX));
     };
-    // Slice g in stage S; NW: loads of W issued after the slice's own; C >= 0:
-    // load W's block C meanwhile.
+    auto store = [&](__amdgpu_buffer_rsrc_t rs, int c, int r, float v) {
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), rs, voff + 128 * (c % 2),
+                                              acc_row(c / 2, r) * n4, W_AUX);
+    };
+    // Slice g in stage S; NW: loads ahead issued after the slice's own; C >= 0:
+    // load block C ahead meanwhile.
     auto step = [&](auto s, auto nw, auto c, int g) {
         constexpr int S = decltype(s)::value, C = decltype(c)::value;
         wait_vm<PER_WAVE * (NS - 2) + decltype(nw)::value>();
@@ -398,20 +404,20 @@ __device__ __forceinline__ void sf_tile_half(float* __restrict__ W, const float*
         // of the multiply.)
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (C >= 0)
-            load_w(C);
+            load_block(ahead_v[C], xr, C);
         __builtin_amdgcn_sched_barrier(0);
         mma(half_stage<S>());
     };
     using std::integral_constant;
     constexpr integral_constant<int, -1> none{};
     constexpr integral_constant<int, 0> zero{};
-    // An interior tile reads W during its first slices, a block per slice, so
-    // that memory works while the matrix cores do (4096 x 4096 at K = 256, two
-    // rounds of tiles: 47-48 us with it, 55-57 without; during the last four
-    // slices instead, 51).
+    // An interior tile reads W (or buf) during its first slices, a block per
+    // slice, so that memory works while the matrix cores do (4096 x 4096 at K =
+    // 256, two rounds of tiles: 47-48 us with it, 55-57 without; during the
+    // last four slices instead, 51).
     constexpr int HEAD = 6;
     static_assert(HEAD % NS == 0 && HEAD >= 4 + NS - 1, "the slices whose waits count loads of W");
-    const bool ahead = !MOM && interior && groups >= HEAD && !ragged;
+    const bool ahead = interior && groups >= HEAD && !ragged;
     if (ragged) {
         // Slice after slice, the groups out of range by bf16 products.
         const unsigned char* const fu = wu.flags + static_cast<int64_t>(pu) * wu.stride;
@@ -462,13 +468,31 @@ __device__ __forceinline__ void sf_tile_half(float* __restrict__ W, const float*
             for (int r = 0; r < 16; ++r)
                 acc[i][j][r] = __builtin_ldexpf(__builtin_fmaf(low[i][j][r], M_UNSCALE, acc[i][j][r]), unscale);
     if (ahead) {
+        if constexpr (MOM) {
+            // W goes where the second accumulators were, all its loads at once
+            // (against half a block of W and buf at a time, nothing ahead:
+            // 4096 x 4096 at K = 512 107 -> 101 us, 21841 x 4096 418 -> 398,
+            // 4100 x 5000 at K = 300 178 -> 145).
+            float w[4][16];
 #pragma unroll
-        for (int c = 0; c < 4; ++c)
+            for (int c = 0; c < 4; ++c)
+                load_block(w[c], wr, c);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int r = 0; r < 16; ++r)
-                __builtin_amdgcn_raw_buffer_store_b32(
-                    __builtin_bit_cast(unsigned, fmaf(-lr, acc[c / 2][c % 2][r], wx[c][r])), wr, voff + 128 * (c % 2),
-                    acc_row(c / 2, r) * n4, W_AUX);
+            for (int c = 0; c < 4; ++c)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const float nb = fmaf(mu, ahead_v[c][r], acc[c / 2][c % 2][r]);
+                    store(xr, c, r, nb);
+                    store(wr, c, r, fmaf(-lr, nb, w[c][r]));
+                }
+        } else {
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    store(wr, c, r, fmaf(-lr, acc[c / 2][c % 2][r], ahead_v[c][r]));
+        }
     } else {
         float pre[16];
         epilogue<2, 2, MOM, 0>(acc, pre, wr, buf, M, N, m0, n0, HALF_TILE, HALF_TILE, wm, wn, lrow, lcol, interior, lr,
