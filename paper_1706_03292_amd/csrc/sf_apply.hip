@@ -69,6 +69,15 @@ struct Small {
     static constexpr int BM = 64, BN = 64, BK = 32, WM = 32, WN = 32;
 };
 constexpr int64_t MID_TILES_PER_CU = 2;
+// 64 x 64 tiles of at most this many per CU (two waves per SIMD), given a
+// contraction of at least this depth, take the pipelined split
+// (Direct::mma_piped).  With and without it: at two tiles per CU 1000 x 2048
+// at K = 1024 34.5 against 36.5 us, K = 256 11.3 and 11.3, K = 96 6.8 and 6.8,
+// K = 64 6.0 and 5.9; at one 1000 x 1024 at K = 1024 21.8 and 23.4; at a
+// sixteenth 256 x 256 at K = 128 4.7 and 4.9; at three 1500 x 2048 at K = 512
+// 29.2 and 28.6, at four 2048 x 2048 36.4 and 35.5.
+constexpr int64_t PIPED_TILES_PER_CU = 2;
+constexpr int64_t PIPED_MIN_K = 128;
 
 // ---------------------------------------------------------------------------
 // Register-staged tile for operands beyond 32-bit offsets: K-slices go global
@@ -218,10 +227,11 @@ __device__ __forceinline__ void sf_tile_staged(float* As, float* Bs, float* __re
 // ---------------------------------------------------------------------------
 // How a kernel works one tile: from the operands as they are (fp32 products,
 // or bf16 parts split by the tile), loading PRE values of W ahead of the last
-// K step, or from operands split beforehand.  WAVES: waves per SIMD the kernel
+// K step (PIPE: with the split pipelined), or from operands split beforehand.
+// WAVES: waves per SIMD the kernel
 // is compiled for.  Ws: what its launches need of a split operand.
 // ---------------------------------------------------------------------------
-template <class TL, bool SPLIT, int PRE>
+template <class TL, bool SPLIT, int PRE, bool PIPE = false>
 struct DirectProducts {
     static constexpr int BM = TL::BM, BN = TL::BN;
     static constexpr int THREADS = SfTile<BM, BN, TL::BK, TL::WM, TL::WN>::THREADS;
@@ -234,7 +244,7 @@ struct DirectProducts {
     static __device__ __forceinline__ void tile(float* W, const float* U, const float* V, int64_t M, int64_t N,
                                                 int64_t K, float lr, int tm, int tn, float* buf, float mu, Ws, Ws)
     {
-        sf_tile_direct<BM, BN, TL::BK, TL::WM, TL::WN, SPLIT, MOM, PRE>(W, U, V, M, N, K, lr, tm, tn, buf, mu);
+        sf_tile_direct<BM, BN, TL::BK, TL::WM, TL::WN, SPLIT, MOM, PRE, PIPE>(W, U, V, M, N, K, lr, tm, tn, buf, mu);
     }
 };
 
@@ -529,6 +539,16 @@ hipError_t launch_tl(float* W, float* buf, const float* U, const float* V, int64
                 return launch_tiles<HalfProducts, HalfProducts, MOM>(W, buf, U, V, M, N, K, lr, mu, spread_s, false,
                                                                      stream, ws);
             }
+        }
+    }
+    if constexpr (SPLIT && TL::BM == Small::BM) {
+        if (spread_s <= 0.0 && !room && K >= PIPED_MIN_K &&
+            tiles_of<TL>(M, N) <= PIPED_TILES_PER_CU * device_cu_count()) {
+            using X = DirectProducts<TL, true, W_PRE, true>;
+            const int tm = static_cast<int>((M + X::BM - 1) / X::BM), tn = static_cast<int>((N + X::BN - 1) / X::BN);
+            sf_apply_kernel<X, MOM><<<tm * tn, X::THREADS, 0, stream>>>(W, U, V, M, N, K, lr, tm, tn, buf, mu, ws[0],
+                                                                        ws[1]);
+            return hipGetLastError();
         }
     }
     // (The momentum epilogue loads no W ahead anyway.)

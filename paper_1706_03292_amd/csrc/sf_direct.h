@@ -109,10 +109,14 @@ __device__ __forceinline__ constexpr int swz(int k) { return (k & 1) << 3; }
 // loads of the slice visible.
 __device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }   // vmcnt(0)
 
-template <int BM, int BN, int BK, int WM, int WN, bool SPLIT>
+template <int BM, int BN, int BK, int WM, int WN, bool SPLIT, bool PIPE>
 struct Direct {
     using T = SfTile<BM, BN, BK, WM, WN>;
     static constexpr int NT = T::THREADS;
+    static_assert(!PIPE || (SPLIT && T::TM * T::TN == 1), "mma_piped");
+    struct Parts {
+        Split3 a, b;
+    };
     template <int S> static __device__ __forceinline__ float* A() { return LdsStage<BK * BM, S, 0>::ptr(); }
     template <int S> static __device__ __forceinline__ float* B() { return LdsStage<BK * BN, S, 1>::ptr(); }
 
@@ -196,6 +200,54 @@ struct Direct {
         }
     }
 
+    // Split-bf16 step of a wave with one block: the slice's values are read at
+    // once, and each 16 rows are split while the matrix cores work on the 16
+    // before them (`p`; zeros at first), which may be the last slice's.  A wave
+    // of one block has one chain of six products and as much splitting as a
+    // wave of four has per 24, and small layers have only one or two waves per
+    // SIMD: reading, splitting and multiplying followed one another (1000 x
+    // 2048 at K = 1024, 35 us without its loads: 12 of them the split, 14 the
+    // products).  With the two interleaved 36.5 -> 34.5 us, 1000 x 1024 23.4
+    // -> 21.8, 512 x 512 22.5 -> 20.7.  Waves that have three others on their
+    // SIMD to overlap with gain nothing.  Same products in the same order.
+    static constexpr int VALU_PER_MFMA = 18;   // splitting 16 rows of both: 108 (20, 16, 12 and 9 are slower)
+
+    template <int S>
+    static __device__ __forceinline__ void mma_piped(f16v (&acc)[T::TM][T::TN], Parts& p, int wm, int wn, int lane)
+    {
+        const float* a_s = A<S>();
+        const float* b_s = B<S>();
+        const int lrow = lane >> 5, lcol = lane & 31;
+        auto at = [&](const float* s, int ld, int kk, int x) {
+            const int k = kk + lrow;
+            return s[k * ld + ((((x >> 2) ^ swz(k)) << 2) | (x & 3))];
+        };
+        float a[BK / 16][8], b[BK / 16][8];
+#pragma unroll
+        for (int h = 0; h < BK / 16; ++h)
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                a[h][q] = at(a_s, BM, 16 * h + 2 * q, wm + lcol);
+                b[h][q] = at(b_s, BN, 16 * h + 2 * q, wn + lcol);
+            }
+#pragma unroll
+        for (int h = 0; h < BK / 16; ++h) {
+            mma_parts(acc, p);
+            p = {split3(a[h]), split3(b[h])};
+#pragma unroll
+            for (int i = 0; i < 6; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);               // one MFMA
+                __builtin_amdgcn_sched_group_barrier(0x002, VALU_PER_MFMA, 0);   // then VALU
+            }
+        }
+    }
+
+    static __device__ __forceinline__ void mma_parts(f16v (&acc)[T::TM][T::TN], const Parts& p)
+    {
+        const Split3 b[1] = {p.b};
+        split_products<1>(acc[0], p.a, b);
+    }
+
     // fp32 step: the MFMA operands of step kk+2 are read while the matrix
     // cores work on step kk.
     template <int S>
@@ -238,7 +290,7 @@ struct Direct {
     // start slice kt+1 into the other stage (free: every wave has passed the
     // barrier after reading it) and multiply.
     template <int S>
-    static __device__ __forceinline__ void step(f16v (&acc)[T::TM][T::TN], __amdgpu_buffer_rsrc_t ur,
+    static __device__ __forceinline__ void step(f16v (&acc)[T::TM][T::TN], Parts& p, __amdgpu_buffer_rsrc_t ur,
                                                 __amdgpu_buffer_rsrc_t vr, int ldu, int ldv, int kt, int wm, int wn,
                                                 int lane, int tid)
     {
@@ -250,7 +302,10 @@ struct Direct {
         // just before the next step waits for them, and their latency is then
         // hidden only by the other workgroups on the CU.
         __builtin_amdgcn_sched_barrier(0);
-        mma<S>(acc, wm, wn, lane);
+        if constexpr (PIPE)
+            mma_piped<S>(acc, p, wm, wn, lane);
+        else
+            mma<S>(acc, wm, wn, lane);
     }
 };
 
@@ -258,12 +313,12 @@ struct Direct {
 // lives in stage (nkt-1-kt) & 1, so the last slice is always in stage 0 and
 // the loop body and the final step are each emitted once.  An interior tile
 // loads PRE values of W ahead of the last K step.
-template <int BM, int BN, int BK, int WM, int WN, bool SPLIT, bool MOM, int PRE = W_PRE>
+template <int BM, int BN, int BK, int WM, int WN, bool SPLIT, bool MOM, int PRE = W_PRE, bool PIPE = false>
 __device__ __forceinline__ void sf_tile_direct(float* __restrict__ W, const float* __restrict__ U,
                                                const float* __restrict__ V, int64_t M, int64_t N, int64_t K,
                                                float lr, int tm, int tn, float* __restrict__ buf, float mu)
 {
-    using D = Direct<BM, BN, BK, WM, WN, SPLIT>;
+    using D = Direct<BM, BN, BK, WM, WN, SPLIT, PIPE>;
     using T = SfTile<BM, BN, BK, WM, WN>;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -282,6 +337,7 @@ __device__ __forceinline__ void sf_tile_direct(float* __restrict__ W, const floa
     const int ni = static_cast<int>(N);
     const int voff = ((wm + 4 * lrow) * ni + wn + lcol) * 4;
     float wv[16];
+    typename D::Parts p{};
 
     const int nkt = static_cast<int>((K + BK - 1) / BK);
     if (nkt > 0) {
@@ -293,20 +349,25 @@ __device__ __forceinline__ void sf_tile_direct(float* __restrict__ W, const floa
         int kt = 0;
         if ((nkt & 1) == 0) {
             D::template issue<1>(ur, vr, ldu, ldv, 0, tid);
-            D::template step<1>(acc, ur, vr, ldu, ldv, 0, wm, wn, lane, tid);
+            D::template step<1>(acc, p, ur, vr, ldu, ldv, 0, wm, wn, lane, tid);
             kt = 1;
         } else {
             D::template issue<0>(ur, vr, ldu, ldv, 0, tid);
         }
         for (; kt < nkt - 1; kt += 2) {
-            D::template step<0>(acc, ur, vr, ldu, ldv, kt, wm, wn, lane, tid);
-            D::template step<1>(acc, ur, vr, ldu, ldv, kt + 1, wm, wn, lane, tid);
+            D::template step<0>(acc, p, ur, vr, ldu, ldv, kt, wm, wn, lane, tid);
+            D::template step<1>(acc, p, ur, vr, ldu, ldv, kt + 1, wm, wn, lane, tid);
         }
         wait_loads();
         __syncthreads();
         if (!MOM && interior)
             load_w_block(wv, wr, voff, ni * 4, 0, PRE);
-        D::template mma<0>(acc, wm, wn, lane);
+        if constexpr (PIPE) {
+            D::template mma_piped<0>(acc, p, wm, wn, lane);
+            D::mma_parts(acc, p);
+        } else {
+            D::template mma<0>(acc, wm, wn, lane);
+        }
     }
     epilogue<T::TM, T::TN, MOM, PRE>(acc, wv, wr, buf, M, N, m0, n0, BM, BN, wm, wn, lrow, lcol, interior, lr, mu);
 }
