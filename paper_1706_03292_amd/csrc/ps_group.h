@@ -65,8 +65,60 @@ struct PerWorker {
     __device__ const float* operator()(int p) const { return g[p] + (((msg_mask >> p) & 1) ? delta : 0); }
 };
 
-// Sum of the P values of elements e .. e+3, in increasing p.
-template <int PT, bool AL, class Src>
+// The last `rem` (0 to 7) shards, p .. P-1, of NG groups of a run-time P: four,
+// two and one of them behind uniform branches, all loaded before the first is
+// added, in increasing p.  A launch of a few waves per SIMD is bound by the
+// chain of its loads' latencies, and one shard after the other made every one
+// of these a latency of its own.
+template <bool AL, class Src, int NG>
+__device__ inline void add_tail(const Src& src, int P, int p, int rem, const int64_t (&e)[NG], f4 (&s)[NG])
+{
+    f4 t[7][NG];
+    const int p2 = p + (rem & 4);
+    if (rem & 4) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int g = 0; g < NG; ++g)
+                t[c][g] = ld4<AL>(src(p + c) + e[g]);
+    }
+    if (rem & 2) {
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int g = 0; g < NG; ++g)
+                t[4 + c][g] = ld4<AL>(src(p2 + c) + e[g]);
+    }
+    if (rem & 1) {
+#pragma unroll
+        for (int g = 0; g < NG; ++g)
+            t[6][g] = ld4<AL>(src(P - 1) + e[g]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (rem & 4) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int g = 0; g < NG; ++g)
+                s[g] += t[c][g];
+    }
+    if (rem & 2) {
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int g = 0; g < NG; ++g)
+                s[g] += t[4 + c][g];
+    }
+    if (rem & 1) {
+#pragma unroll
+        for (int g = 0; g < NG; ++g)
+            s[g] += t[6][g];
+    }
+}
+
+// Sum of the P values of elements e .. e+3, in increasing p (CHAIN: of a
+// run-time P, the shards behind the last chunk one after another).
+template <int PT, bool AL, bool CHAIN, class Src>
 __device__ inline f4 sum4(const Src& src, int P, int64_t e)
 {
     if constexpr (PT > PS_CHUNK) {
@@ -96,7 +148,8 @@ __device__ inline f4 sum4(const Src& src, int P, int64_t e)
             s += g[p];
         return s;
     } else {
-        f4 s = ld4<AL>(src(0) + e);
+        const int64_t at[1] = {e};
+        f4 s[1] = {ld4<AL>(src(0) + e)};
         int p = 1;
         for (; p + PS_CHUNK <= P; p += PS_CHUNK) {
             f4 g[PS_CHUNK];
@@ -105,21 +158,28 @@ __device__ inline f4 sum4(const Src& src, int P, int64_t e)
                 g[c] = ld4<AL>(src(p + c) + e);
 #pragma unroll
             for (int c = 0; c < PS_CHUNK; ++c)
-                s += g[c];
+                s[0] += g[c];
         }
-        for (; p < P; ++p)
-            s += ld4<AL>(src(p) + e);
-        return s;
+        if constexpr (CHAIN) {
+            for (; p < P; ++p)
+                s[0] += ld4<AL>(src(p) + e);
+        } else {
+            add_tail<AL>(src, P, p, P - p, at, s);
+        }
+        return s[0];
     }
 }
 
-// The update of elements e .. min(e + 4, end) - 1 of one tensor.
-template <int PT, bool MOM, bool AL, class Src>
+// The update of elements e .. min(e + 4, end) - 1 of one tensor.  (CHAIN for
+// the batched pass and the KV store, whose one group per thread leaves waves
+// enough: without it the batched pass at P = 7 took 13.9 us for 1.0M values
+// where it takes 13.2, and 118 for 15M where it takes 114.)
+template <int PT, bool MOM, bool AL, bool CHAIN = true, class Src>
 __device__ inline void apply_group(float* __restrict__ W, float* __restrict__ buf, const Src& src, int P, int64_t e,
                                    int64_t end, float lr, float mu)
 {
     if (e + 3 < end) {
-        const f4 s = sum4<PT, AL>(src, P, e);
+        const f4 s = sum4<PT, AL, CHAIN>(src, P, e);
         f4 w = ld4<AL>(W + e);
         if constexpr (MOM) {
             const f4 b = fma4(mu, ld4<AL>(buf + e), s);
@@ -149,25 +209,32 @@ __device__ inline void apply_group(float* __restrict__ W, float* __restrict__ bu
 
 // Two groups of one tensor, e and e + PS_PAIR_GAP (64 lanes' groups apart, so
 // that a wave's two accesses to each array read 2 KB in a row instead of
-// 1 KB; the single-tensor launch): when both are whole and P is a
-// compile-time value, their loads are issued together, PS_PAIR_CHUNK shards
-// at a time; otherwise the two groups are applied one after the other.  Per element the arithmetic and its order
+// 1 KB; the single-tensor launch): when both are whole their loads are issued
+// together, PS_PAIR_CHUNK shards at a time (PS_CHUNK when P is a run-time
+// value); otherwise the two groups are applied one after the other.  Per element the arithmetic and its order
 // are apply_group's, so the results are the same, bitwise.  Single-tensor
 // launches of 2,621,440 values at P = 32 ran at 5.97-6.03 TB/s against
 // 5.49 with one group per thread, 4,194,304 values at P = 8 at 5.43-5.57
 // against 4.85-4.90, and 2,359,296 values at P = 16 measured the same
-// (5.45-5.54 against 5.46-5.62).
+// (5.45-5.54 against 5.46-5.62).  A run-time P with its two groups together and
+// add_tail, against one group after the other and one shard of the tail after
+// another, momentum included: 1,179,648 values at P = 7 10.6 against 12.2 us
+// and at P = 15 17.2 against 18.7, 1,179,649 at P = 12 14.75 against 16.5 and at
+// P = 31 31.0 against 34.7 (4.9 TB/s), 6,000,001 at P = 20 98.9 against 110.4;
+// add_tail with the groups one after the other 1-10% slower.  CHAIN keeps that
+// earlier order (see ps_chain).
 constexpr int64_t PS_PAIR_GAP = 256;
 constexpr int PS_PAIR_CHUNK = 4;
 
-template <int PT, bool MOM, bool AL, class Src>
+template <int PT, bool MOM, bool AL, bool CHAIN = false, class Src>
 __device__ inline void apply_pair(float* __restrict__ W, float* __restrict__ buf, const Src& src, int P, int64_t e,
                                   int64_t end, float lr, float mu)
 {
     const int64_t e1 = e + PS_PAIR_GAP;
-    if constexpr (PT > 0) {
-        if (e1 + 3 < end) {
-            f4 s0 = ld4<AL>(src(0) + e), s1 = ld4<AL>(src(0) + e1);
+    if (!CHAIN && e1 + 3 < end) {
+        const int64_t at[2] = {e, e1};
+        f4 s[2] = {ld4<AL>(src(0) + e), ld4<AL>(src(0) + e1)};
+        if constexpr (PT > 0) {
 #pragma unroll
             for (int p0 = 1; p0 < PT; p0 += PS_PAIR_CHUNK) {
                 f4 a[PS_PAIR_CHUNK], b[PS_PAIR_CHUNK];
@@ -180,32 +247,62 @@ __device__ inline void apply_pair(float* __restrict__ W, float* __restrict__ buf
 #pragma unroll
                 for (int c = 0; c < PS_PAIR_CHUNK; ++c)
                     if (p0 + c < PT) {
-                        s0 += a[c];
-                        s1 += b[c];
+                        s[0] += a[c];
+                        s[1] += b[c];
                     }
                 // one chunk of both groups in registers at a time
                 __builtin_amdgcn_sched_barrier(0);
             }
-            f4 w0 = ld4<AL>(W + e), w1 = ld4<AL>(W + e1);
-            if constexpr (MOM) {
-                const f4 b0 = fma4(mu, ld4<AL>(buf + e), s0);
-                const f4 b1 = fma4(mu, ld4<AL>(buf + e1), s1);
-                st4<AL>(buf + e, b0);
-                st4<AL>(buf + e1, b1);
-                w0 = fma4(-lr, b0, w0);
-                w1 = fma4(-lr, b1, w1);
-            } else {
-                w0 = fma4(-lr, s0, w0);
-                w1 = fma4(-lr, s1, w1);
+        } else {
+            int p = 1;
+            for (; p + PS_CHUNK <= P; p += PS_CHUNK) {
+                f4 a[PS_CHUNK], b[PS_CHUNK];
+#pragma unroll
+                for (int c = 0; c < PS_CHUNK; ++c) {
+                    a[c] = ld4<AL>(src(p + c) + e);
+                    b[c] = ld4<AL>(src(p + c) + e1);
+                }
+#pragma unroll
+                for (int c = 0; c < PS_CHUNK; ++c) {
+                    s[0] += a[c];
+                    s[1] += b[c];
+                }
             }
-            st4<AL>(W + e, w0);
-            st4<AL>(W + e1, w1);
-            return;
+            add_tail<AL>(src, P, p, P - p, at, s);
         }
+        f4 w0 = ld4<AL>(W + e), w1 = ld4<AL>(W + e1);
+        if constexpr (MOM) {
+            const f4 b0 = fma4(mu, ld4<AL>(buf + e), s[0]);
+            const f4 b1 = fma4(mu, ld4<AL>(buf + e1), s[1]);
+            st4<AL>(buf + e, b0);
+            st4<AL>(buf + e1, b1);
+            w0 = fma4(-lr, b0, w0);
+            w1 = fma4(-lr, b1, w1);
+        } else {
+            w0 = fma4(-lr, s[0], w0);
+            w1 = fma4(-lr, s[1], w1);
+        }
+        st4<AL>(W + e, w0);
+        st4<AL>(W + e1, w1);
+        return;
     }
-    apply_group<PT, MOM, AL>(W, buf, src, P, e, end, lr, mu);
+    apply_group<PT, MOM, AL, CHAIN>(W, buf, src, P, e, end, lr, mu);
     if (e1 < end)
-        apply_group<PT, MOM, AL>(W, buf, src, P, e1, end, lr, mu);
+        apply_group<PT, MOM, AL, CHAIN>(W, buf, src, P, e1, end, lr, mu);
+}
+
+// Whether a single-tensor launch keeps one group and one shard of the tail
+// after another.  Tensors with waves enough to hide that latency gain nothing
+// from more loads in flight, and where most of P is tail lose by them: with
+// momentum, 4,194,304 values at P = 5 24.8 us this way against 25.9, at P = 7
+// 29.6 against 31.6, 3,100,000 at P = 15 39.2 against 40.4, 2,359,296 at P = 6
+// 16.5 against 16.8 (P = 9 at 4,194,304 41.9 against 38.2 and P = 12 48.3 against
+// 46.8: those don't); 1,700,000 at P = 3 10.0 against 9.6, at P = 7 14.5 against
+// 13.7, at P = 15 24.1 against 22.7.
+constexpr int64_t PS_CHAIN_ABOVE = int64_t{1} << 21;
+inline bool ps_chain(int32_t P, int64_t n)
+{
+    return n > PS_CHAIN_ABOVE && (P < 8 || (P > 12 && P < 16));
 }
 
 }  // namespace poseidon
