@@ -29,8 +29,7 @@ if ROOT not in sys.path:
 METRIC = "per-iteration sync ms; SFB TFLOP/s + PS apply GB/s vs roofline at P=16"
 PEAK_FP32_MFMA_TFLOPS = 157.3     # MI355X dense fp32 matrix peak
 PEAK_BF16_MFMA_TFLOPS = 2500.0    # MI355X dense bf16 matrix peak
-SPLIT_PRODUCTS = 6                # bf16 products per fp32 multiply-add of operands split by the tiles
-HALF_PRODUCTS = 3                 # fp16 products per fp32 multiply-add of operands split beforehand
+SPLIT_PRODUCTS = 6                # bf16 products per fp32 multiply-add with the split arithmetic
 PEAK_HBM_GBS = 8000.0             # MI355X HBM3E
 
 
@@ -79,7 +78,7 @@ def _ps_bytes(spec, P, momentum: bool):
 
 # Sources whose device code a kernel's counter figures depend on, besides
 # the file named: the PS kernels' per-group update lives in a shared header.
-_KERNEL_EXTRA_SOURCES = {"ps_apply.hip": ["ps_group.h"], "sf_apply.hip": ["sf_tile.h", "sf_direct.h", "sf_half.h"]}
+_KERNEL_EXTRA_SOURCES = {"ps_apply.hip": ["ps_group.h"]}
 
 
 def _kernel_source_hash(name: str) -> str:
@@ -273,24 +272,13 @@ def _cpu_baseline(wl, host, fraction, min_seconds):
     }
 
 
-def _split_beforehand(M, N, K):
-    """Whether the library splits this layer's operands beforehand (256 CUs)."""
-    tiles = -(-M // 128) * -(-N // 128)
-    return tiles >= 512 and K >= 128 and 2.0 * M * N * K >= 4e9 and M * N >= 256 * (M + N)
-
-
-def _sf_peak(arith, halves):
+def _sf_peak(arith):
     """The SF kernel's matrix-core ceiling in contraction flops (2MNK): the
-    fp32 peak, or the 16-bit peak over the products the split arithmetic forms
-    per fp32 multiply-add (`halves`: every layer is split beforehand)."""
+    fp32 peak, or the bf16 peak over the six products the split arithmetic
+    forms per fp32 multiply-add."""
     from paper_1706_03292_amd import api
     if arith == api.SF_FP32:
         return PEAK_FP32_MFMA_TFLOPS, "fp32 MFMA (v_mfma_f32_32x32x2_f32)"
-    if halves:
-        return (PEAK_BF16_MFMA_TFLOPS / HALF_PRODUCTS,
-                "split-fp16 MFMA (v_mfma_f32_32x32x16_f16): each fp32 operand split beforehand into two scaled fp16 "
-                f"parts, {HALF_PRODUCTS} products per fp32 multiply-add, fp32 accumulation; peak = "
-                f"{PEAK_BF16_MFMA_TFLOPS:.0f} 16-bit TFLOP/s / {HALF_PRODUCTS}")
     return (PEAK_BF16_MFMA_TFLOPS / SPLIT_PRODUCTS,
             "split-bf16 MFMA (v_mfma_f32_32x32x16_bf16): each fp32 operand split exactly into three bf16 parts, "
             f"six part products per fp32 multiply-add, fp32 accumulation; peak = {PEAK_BF16_MFMA_TFLOPS:.0f} "
@@ -332,7 +320,7 @@ def _sf_phase(wl, host, devt, schemes, launch_ms, time_fn, stream):
     tflops = flops / in_ms / 1e9 if in_ms else None
     how = (f"the grouped launch of the {len(idx)} SFB layers inside the iteration ({grouped_ms:.4f} ms)"
            if grouped_ms else f"the summed average durations of their launches inside the iteration ({in_ms:.4f} ms)")
-    peak, arith_name = _sf_peak(api.sf_arithmetic(), all(_split_beforehand(*host[i]["spec"].shape, wl.K) for i in idx))
+    peak, arith_name = _sf_peak(api.sf_arithmetic())
     return {
         "in_iteration_ms": in_ms,
         "layers": layers,
@@ -676,7 +664,7 @@ def main():
         "higher_is_better": False,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "f32" if api.sf_arithmetic() == api.SF_FP32 else "f32 (SF products: fp16x3 / bf16x6 split)",
+        "dtype": "f32" if api.sf_arithmetic() == api.SF_FP32 else "f32 (SF products: bf16x6 split)",
         "data": "synthetic",
         "config": {"workload": f"{wl.name}: {sum(s.numel for s in wl.specs)} params, "
                                f"{len(wl.specs)} tensors, K={wl.K}, lr={wl.lr}, momentum={wl.momentum}",

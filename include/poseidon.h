@@ -14,18 +14,10 @@
  *
  * General conventions
  *  - All array arguments are device pointers to fp32 data owned by the caller.
- *    The library keeps no pointer past a call,
+ *    The library allocates no device memory and keeps no pointer past a call,
  *    except a KV store, which keeps its tensors' pointers for its lifetime and
  *    each received update's pointer until the work it triggers has been
  *    enqueued (and the caller keeps that memory valid until the work has run).
- *  - Rebuilds of large SFB layers (from two 128 x 128 tiles per CU and 4 GFLOP
- *    up) split their factors into scratch device memory of 4 bytes per value
- *    first.  The library keeps it per stream between calls (at most 4 GiB per
- *    device, or one launch's need where that is more) and frees it when a
- *    stream pool is destroyed; a call on a capturing stream takes memory that
- *    belongs to the graph instead.  A stream a rebuild was enqueued on has
- *    drained before it is destroyed.  Where the memory cannot be had, the
- *    rebuild forms its products as for smaller layers.
  *  - Work is enqueued asynchronously on `stream` (0 = the null stream).
  *    Argument errors are detected and reported synchronously, before anything
  *    is enqueued; a fault inside a kernel surfaces at the next synchronisation
@@ -93,9 +85,10 @@ extern "C" {
  *     worker p are contiguous.
  * The sum is accumulated in fp32 on the matrix cores and W is read and written
  * exactly once.  lr is applied as given (no 1/(P*B) scaling).  The products
- * are formed as poseidon_sf_set_arithmetic last chose: by default from split
- * operands on the 16-bit matrix cores (fp32-grade); POSEIDON_SF_FP32 uses the
- * fp32 matrix-core product.
+ * are formed as poseidon_sf_set_arithmetic last chose: by default each fp32
+ * operand is split exactly into three bf16 parts and six of their nine
+ * products are accumulated (fp32-grade: the three left out are below 2^-23
+ * of the product); POSEIDON_SF_FP32 uses the fp32 matrix-core product.
  * Operands whose byte offsets exceed 32 bits always take the fp32 product.
  * Returns POSEIDON_OK, POSEIDON_ERR_INVALID_ARG (negative size, NULL pointer
  * with nonzero size, W overlapping U or V) or POSEIDON_ERR_HIP.
@@ -130,14 +123,7 @@ int poseidon_sf_apply_momentum(float* W, float* buf, const float* U, const float
  * into bf16 parts h + m + l (h and m rounded to nearest, l the remainder,
  * which has at most 8 significant bits) and accumulates the six products
  * h*h, h*m, m*h, h*l, l*h and m*m in fp32 on the bf16 matrix cores (the six-
- * product split of Henry, Tang and Heinecke, ARITH 2019).  In large layers the
- * values of a 64-column panel that lie within 2^-25 .. 2^3 of the panel's
- * largest are split, scaled by a power of two, into two fp16 parts instead
- * and the products h*h, h*m and m*h accumulated in fp32 (each operand to
- * within one unit of fp32's last place, the product left out below 2^-22 of
- * the value's, the sum with a third of the roundings); 16 rows of K at a time
- * take the six products where a panel holds other values, and a tile all of
- * them where one is above that range.  POSEIDON_SF_FP32
+ * product split of Henry, Tang and Heinecke, ARITH 2019); POSEIDON_SF_FP32
  * accumulates the fp32 matrix-core products.  The two agree to fp32
  * rounding on finite operands below 3.39e38 in magnitude (the largest bf16);
  * an infinite or larger operand makes the outputs it reaches NaN with the
@@ -165,8 +151,7 @@ typedef struct poseidon_sf_tensor {
  * poseidon_sf_apply(W, U, V, M, N, K, lr).  Their tiles form one work list
  * (in the order given), so the GPU is never left half idle between layers;
  * layers whose rows are too long for the grouped kernel, and groups too small
- * to fill the GPU, are launched one by one instead, and layers whose factors
- * are split beforehand share a list of their own.  The W arrays must not
+ * to fill the GPU, are launched one by one instead.  The W arrays must not
  * overlap each other or any U, V.  All layers are validated before anything
  * is enqueued.  Returns POSEIDON_OK, POSEIDON_ERR_INVALID_ARG (as for
  * poseidon_sf_apply, for any layer; count < 0; NULL layers with count > 0;
@@ -465,20 +450,21 @@ int poseidon_pool_destroy(poseidon_stream_pool* pool);
  * kinds overlap -- the kind with the longer estimated time (at the rates
  * below) on the caller's `stream` itself, the other on the pool's first
  * stream, forked from and joined back to `stream`; a one-stream pool, an iteration
- * whose work would take under 30 us at the kernels' rates (300 TFLOP/s for
- * large SFB layers, 140 for others, 130 with fp32 products; 5 TB/s for PS), one
- * whose smaller kind would take under 8 us, or one whose kinds only delay each
- * other (the applies the longer kind and the rebuilds above 0.22 of them; with
- * fp32 products the smaller kind above 0.35 of the larger) runs everything in
- * order on one stream (without ready events the caller's `stream` itself, with no
+ * whose work would take under 30 us at the kernels' rates (130 TFLOP/s for
+ * SFB, 5 TB/s for PS), or one whose two kinds would take comparable times at
+ * those rates (the smaller above 0.35 of the larger: neither leaves gaps the
+ * other could fill, so co-running only delays both) runs everything in order
+ * on one stream (without ready events the caller's `stream` itself, with no
  * fork and join events).  Two kinds of tensors share launches instead (with
  * the kernels and arithmetic of the single-tensor calls, so the same
  * results): PS tensors of
  * fewer than 2^17 values, which a launch of their own would leave
  * latency-bound, are applied together, in backpropagation order, by one
  * batched pass (poseidon_ps_apply_batch) after the other PS launches -- and
- * when the PS applies are the iteration's critical path (the longer kind at
- * those rates), so do PS tensors of fewer than 2^21 values; and the SFB tensors without a momentum buffer, when there are
+ * when the PS applies are the iteration's critical path (the SFB rebuilds
+ * come to fewer than 26 flops per PS byte, 2*M*N*P*B flops against
+ * n*(4P+16) bytes, or 4P+8 without a buffer), so do PS tensors of fewer than
+ * 2^21 values; and the SFB tensors without a momentum buffer, when there are
  * several, are rebuilt by one grouped launch (poseidon_sf_apply_batch) at the
  * place of the first of them, so that the layers' tiles share one work list
  * -- except in a two-stream iteration whose PS applies are the longer kind:
@@ -486,7 +472,7 @@ int poseidon_pool_destroy(poseidon_stream_pool* pool);
  * its tiles, sized to take about 90% of the applies' estimated time, so that
  * the rebuilds run thin beside the applies.  Conversely, when the SFB
  * rebuilds are the longer kind (and the applies would still end first at
- * the rate they get beside them: 1.9 TB/s beside the split rebuild,
+ * the rate they get beside them: 1.9 TB/s beside the split-bf16 rebuild,
  * 1.3 beside the fp32 one), the rebuilds leave each SIMD the registers of
  * more waves and the PS applies of aligned tensors use a low-register kernel
  * that runs in them, on the CUs the rebuilds keep busy.  Every variant

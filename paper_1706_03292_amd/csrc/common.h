@@ -67,14 +67,10 @@ void set_sf_arithmetic(int32_t arithmetic);
 
 // The time the iteration's stream policy assumes for one layer's rebuild,
 // from the rates measured alone on one MI355X (fp32-equivalent contraction
-// flops): with operands split beforehand 10 us for that pass and the start,
-// and 300 TFLOP/s or W read and written at 4 TB/s (21841 x 4096 at K = 512 in
-// 310 us, 4096 x 4096 at K = 512 in 68 and at K = 256 in 48); six bf16
-// products about 140 (the 4096 x 4096 layer at K = 256: 142); fp32 products
-// 124-138.
-constexpr double SF_PRESPLIT_S = 10e-6;
-constexpr double SF_HALF_FLOPS_PER_S = 3.0e14;
-constexpr double SF_HALF_W_BYTES_PER_S = 4.0e12;
+// flops): split-bf16 products on 256 x 128 tiles 186-194 TFLOP/s (the
+// grouped VGG19-22K FC launch), on smaller tiles about 140 (the 4096 x 4096
+// layer at K = 256: 142); fp32 products 124-138.
+constexpr double SF_SPLIT_BIG_FLOPS_PER_S = 1.85e14;
 constexpr double SF_SPLIT_FLOPS_PER_S = 1.4e14;
 constexpr double SF_FP32_FLOPS_PER_S = 1.3e14;
 double sf_seconds(int64_t M, int64_t N, int64_t K);
@@ -83,9 +79,8 @@ double sf_seconds(int64_t M, int64_t N, int64_t K);
 // spread_s > 0, an SF launch runs on as few workgroups as would walk its
 // tiles in about spread_s seconds, instead of one workgroup per tile.  Given
 // `room`, the SF tiles leave each SIMD the registers of a wave of the lean PS
-// kernel beside theirs (the tiles of operands split beforehand always do), and
-// a PS launch given `beside_sf` uses that kernel (aligned tensors), so that the
-// two run on the same CUs.
+// kernel beside theirs, and a PS launch given `beside_sf` uses that kernel
+// (aligned tensors), so that the two run on the same CUs.
 hipError_t launch_sf_apply(float* W, const float* U, const float* V,
                            int64_t M, int64_t N, int64_t K, float lr, hipStream_t stream, double spread_s = 0.0,
                            bool room = false);

@@ -81,19 +81,19 @@ __global__ __launch_bounds__(PS_THREADS) void ps_apply_kernel(float* __restrict_
 }
 
 // ---------------------------------------------------------------------------
-// One tensor beside the SF rebuild.  The fp32 rebuild's tiles, launched with
-// room for it, take 118 VGPRs, so a SIMD's four SF waves leave it 32; a wave of
+// One tensor beside the SF rebuild.  The rebuild's tiles, launched with room
+// for it, take 118 VGPRs, so a SIMD's four SF waves leave it 32; a wave of
 // this kernel takes 22: one VGPR offset shared by all of a thread's accesses
 // (buffer loads, the shard stride in the scalar offset), the shard loads
 // LEAN_CHUNK at a time.  It therefore runs on the CUs the rebuild keeps busy,
 // streaming memory while the matrix cores work, instead of waiting for a
-// rebuild workgroup's slot to free up (VGG19-22K iteration with fp32 products
-// 1.702-1.710 -> 1.659-1.675 ms).  Its workgroups walk the tensor grid-stride:
-// one per CU beside the fp32 rebuild, two beside the split one, whose two
-// waves of 232 registers leave each SIMD 48 (VGG19-22K at P = 4, B = 32, whose
-// applies are short next to the rebuild: 0.457 ms with two per CU, 0.462 with
-// one, 0.500 with one per two CUs).  The arithmetic and its order are
-// apply_group's: the same results, bitwise.  Aligned tensors whose
+// rebuild workgroup's slot to free up (VGG19-22K iteration 1.702-1.710 ->
+// 1.659-1.675 ms).  Its workgroups walk the tensor grid-stride: one per CU
+// beside the fp32 rebuild, one per two CUs beside the split-bf16 one, whose
+// matrix-core work the applies then slow less (VGG19-22K iteration
+// 1.231-1.237 ms against 1.237-1.245 with one per CU and 1.242-1.250 with
+// two; 3/8 and 5/8 of the CUs measured as one half).  The arithmetic and its
+// order are apply_group's: the same results, bitwise.  Aligned tensors whose
 // P*n*4 bytes fit 31-bit buffer offsets.
 // ---------------------------------------------------------------------------
 constexpr int LEAN_CHUNK = 4;
@@ -158,7 +158,7 @@ hipError_t launch_pt(float* W, const float* G, int32_t P, int64_t n, float lr, f
     if (beside_sf && al && static_cast<int64_t>(P) * n * 4 <= 0x7fffffffLL) {
         const int64_t want = (n / 4 + PS_THREADS - 1) / PS_THREADS;
         const int64_t cus = device_cu_count();
-        const int64_t grid = sf_arithmetic() == POSEIDON_SF_FP32 ? cus : 2 * cus;
+        const int64_t grid = sf_arithmetic() == POSEIDON_SF_FP32 ? cus : (cus + 1) / 2;
         ps_apply_lean_kernel<PT, MOM><<<static_cast<int>(want < grid ? want : grid), PS_THREADS, 0, stream>>>(
             W, G, P, static_cast<int>(n), lr, mu, buf);
         return hipGetLastError();

@@ -12,7 +12,6 @@
 #include <vector>
 
 #include "common.h"
-#include "scratch.h"
 
 struct poseidon_stream_pool {
     int device = -1;
@@ -120,10 +119,8 @@ extern "C" int poseidon_pool_create(int32_t num_streams, poseidon_stream_pool** 
 
 extern "C" int poseidon_pool_destroy(poseidon_stream_pool* pool)
 {
-    if (pool) {
+    if (pool)
         destroy_pool(pool);
-        poseidon::scratch_give_back();
-    }
     return POSEIDON_OK;
 }
 
@@ -148,23 +145,19 @@ constexpr double PS_BYTES_PER_S = 5.0e12;   // the PS kernel's rate on this GPU 
 // overlap gains (a 1024 x 512 FC layer and a 1M-value PS layer at P = 4:
 // 0.033 ms on one stream, 0.043-0.053 ms on two).
 constexpr double ONE_STREAM_BELOW_S = 30e-6;
-// Two streams pay when one kind of update fills what the other leaves idle.
-// With the split products that is so whenever the rebuilds are the longer
-// kind: they leave memory bandwidth, the applies take it (VGG19-22K, the
-// smaller estimated time 0.41 of the larger: 0.937 ms on two streams, 0.990 on
-// one; the same layers with 16 workers of batch 16, 0.64: 0.702 against
-// 0.750).  When the applies are the longer kind they leave the rebuilds little
-// but to run thin beside them, which pays for a small rebuild only (the
-// Inception-shaped workload, 0.05: 0.623 against 0.650; the 4096 x 4096 layer
-// at K = 256 beside 805 MB of applies, 0.27: 0.193 against 0.189; VGG19-22K at
-// K = 64 beside 1.44 GB, 0.66: 0.640 against 0.614).  The fp32 products keep
-// the matrix cores busier: there two streams lose above 0.35 either way (that
-// 4096 x 4096 layer, 0.236 against 0.222).
-constexpr double CORUN_SF_LONGER = 1.0, CORUN_PS_LONGER = 0.22, CORUN_FP32 = 0.35;
-// A kind of less than this gains nothing that the fork and the join do not
-// cost (the Inception-shaped list at P = 8, its rebuild 7 us: 0.217 ms on one
-// stream, 0.230 on two).
-constexpr double FORK_MIN_S = 8e-6;
+// Two streams pay when one kind of update is small next to the other: the
+// small one's launches fill the gaps the large one leaves (its tile rounds'
+// ends, the last partial round), and take little from it.  When the two are
+// of comparable size neither has gaps to fill, and the co-running launches
+// only delay each other: the 4096 x 4096 layer rebuilt at K = 256 (one round
+// of tiles, 0.083 ms alone with fp32 products, 0.060 split) beside 805 MB of
+// PS applies (0.139-0.152 ms alone) took 0.236 ms on two streams against
+// 0.222 ms one after the other (split: 0.216 against 0.206).  Below this
+// ratio of the smaller estimated time to the larger the iteration uses two
+// streams (VGG19-22K: 0.27 split, 0.19 fp32, two streams 1.24 ms against
+// 1.37 on one, split; the Inception-shaped workload: 0.05; that 4096 x 4096
+// layer through both schemes: 0.38 split, 0.41 fp32).
+constexpr double CORUN_MAX_RATIO = 0.35;
 // When the PS applies are the longer kind on two streams, every SF launch is
 // spread over few workgroups that walk its tiles, given this fraction of the
 // applies' estimated time (each layer its share by flops): thin beside the
@@ -179,13 +172,12 @@ constexpr double SF_SPREAD_OF_PS = 0.9;
 // applies use it, so that they stream memory on the CUs the rebuilds keep
 // busy -- provided the applies still end before the rebuilds: at the lean
 // kernel's rate beside them they must take at most this fraction of the
-// rebuilds' estimated time.  That rate is set by the lean kernel's grid and
-// by the waves that fit beside the rebuild's (two workgroups per CU beside the
-// split rebuild's two waves of 232 VGPRs per SIMD; one, one wave per SIMD,
-// beside the fp32 128 x 128 tiles' four of 120: VGG19-22K's largest PS tensors,
-// 189 MB, in 0.141 ms).  Beside the split rebuild the applies of VGG19-22K at P
-// = 16 measured the same either way (0.930-0.949 ms lean, 0.937 not), at P = 4
-// 0.457 against 0.481 one after the other.
+// rebuilds' estimated time.  That rate is set by the lean kernel's grid
+// (one workgroup on every second CU beside the split-bf16 rebuild: its
+// 256 x 128 tiles' two waves of 228 VGPRs per SIMD; VGG19-22K's largest PS
+// tensors, 189 MB, in 0.10 ms) and by the waves that fit beside the rebuild's
+// (one workgroup per CU, one wave per SIMD beside the fp32 128 x 128 tiles'
+// four of 120; 0.141 ms).
 constexpr double LEAN_PS_BYTES_PER_S_SPLIT = 1.9e12;
 constexpr double LEAN_PS_BYTES_PER_S_FP32 = 1.3e12;
 constexpr double LEAN_OF_SF = 0.85;
@@ -322,11 +314,7 @@ int sync_impl(poseidon_stream_pool* pool, const poseidon_tensor* tensors, int32_
     const bool tiny = t_sf + t_ps < ONE_STREAM_BELOW_S;
     // With ready events the second stream also lets the updates start while
     // the caller's backward pass still runs, so it is kept.
-    const double corun = sf_arithmetic() == POSEIDON_SF_FP32 ? CORUN_FP32
-                         : t_sf >= t_ps                      ? CORUN_SF_LONGER
-                                                             : CORUN_PS_LONGER;
-    const double t_min = std::min(t_sf, t_ps);
-    const bool balanced = !per && (t_min < FORK_MIN_S || t_min > corun * std::max(t_sf, t_ps));
+    const bool balanced = !per && std::min(t_sf, t_ps) > CORUN_MAX_RATIO * std::max(t_sf, t_ps);
     // Spread SF launches (below) replace the grouped one; under the held
     // schedule the launches are the plain iteration's, spread included.
     const bool spread = (!ready || all_last) && S > 1 && !tiny && !balanced && t_ps > t_sf && sf_flops > 0.0;

@@ -1,6 +1,8 @@
-"""GPU parity of the SF rebuild with operands split beforehand into fp16 parts
-(layers of at least two 128 x 128 tiles per CU and 4 GFLOP): the edges of its
-tiles, K groups and value ranges, and the scratch memory its streams keep."""
+"""GPU parity of the SF rebuild of large layers (at least two 128 x 128 tiles
+per CU): the edges of their tiles and K slices, the precision of sums of few
+products and of values of any size, rebuilds from several streams and threads,
+and what a rebuild must not cost: time that depends on the factors' values, and
+device memory of the library's own."""
 import threading
 
 import numpy as np
@@ -15,18 +17,17 @@ from paper_1706_03292_amd import inputs as I
 pytestmark = pytest.mark.gpu
 
 
-# K of 8, 9 and 10 groups of 16 rows (the ring of three stages ends in each of
-# its stages), whole and partial; M and N one past a tile, one short of one,
-# and with the tile's second panel outside the matrix.
+# K of 8, 9 and 10 slices of 16 rows, whole and partial; M and N one past a
+# tile, one short of one, and with half of the last tile outside the matrix.
 @pytest.mark.parametrize("M,N,K", [(4096, 4096, 128), (4097, 4160, 129), (4095, 4161, 144), (4224, 4033, 160),
                                    (2049, 8200, 143)])
 @pytest.mark.parametrize("momentum", [False, True])
-def test_sf_half_edges(M, N, K, momentum):
+def test_sf_large_edges(M, N, K, momentum):
     d = dev()
     W, U, V = I.randn(M + K, (M, N), 0.01), I.randn(M + K + 1, (K, M), 0.1), I.randn(M + K + 2, (K, N), 0.1)
     buf = I.randn(M + K + 3, (M, N), 1e-3)
     rows, cols = sample_points(M, N, 3000, seed=N)
-    log(f"sf half M={M} N={N} K={K} momentum={momentum}")
+    log(f"sf large M={M} N={N} K={K} momentum={momentum}")
     Wd, Ud, Vd = W.to(d), U.to(d), V.to(d)
     if momentum:
         bd = buf.to(d)
@@ -48,9 +49,9 @@ def test_sf_half_edges(M, N, K, momentum):
 
 
 def _plant(kind, U, V):
-    """Values that leave the range of a panel's fp16 parts."""
+    """Values far from the rest of their 64 columns, up to the ends of fp32's range."""
     K, M = U.shape
-    if kind == "tiny":               # below it: alone in their row of the gradient, and among others
+    if kind == "tiny":               # small ones: alone in their row of the gradient, and among others
         U[:, 5] = 0
         U[K - 1, 5] = 1e-12          # the partial last group
         U[3, 200] = -3e-11
@@ -59,22 +60,22 @@ def _plant(kind, U, V):
         V[0, 4098] = 1e-20
     elif kind == "subnormal":        # and below fp32's normal numbers
         V[9, 9] = 1e-42
-    elif kind == "large":            # above it, in one panel
+    elif kind == "large":            # a large one
         U[20, 130] = 3e7
-    elif kind == "zeros":            # whole panels and groups of zeros are in range
+    elif kind == "zeros":            # whole columns and slices of zeros
         U[:, 64:128] = 0
         V[16:32] = 0
-    elif kind == "scales":           # panels of very different size
+    elif kind == "scales":           # columns of very different size
         U[:, 128:192] *= 2.0 ** 50
         V[:, :64] *= 2.0 ** -45
-    elif kind == "extreme":          # panels beyond the exponents that are scaled at all
+    elif kind == "extreme":          # and further apart
         U[:, 0:64] *= 2.0 ** 90
         V[:, 64:128] *= 2.0 ** -90
     return U, V
 
 
 @pytest.mark.parametrize("kind", ["tiny", "subnormal", "large", "zeros", "scales", "extreme"])
-def test_sf_half_values_out_of_range_stay_fp32_grade(kind):
+def test_sf_large_values_of_any_size_stay_fp32_grade(kind):
     """Per element the raw gradient stays within 2 sqrt(K) + 16 units of 2^-24
     of sum_k |U[k][m]| |V[k][n]| (fp32 rounding in any order of summation), also
     where that sum consists of values far below the rest of their panel."""
@@ -92,7 +93,7 @@ def test_sf_half_values_out_of_range_stay_fp32_grade(kind):
     units = {}
     for arith in (api.SF_BF16X6, api.SF_FP32):
         Z = torch.zeros(M, N, device=d)
-        log(f"sf half values {kind} arithmetic {arith}")
+        log(f"sf large values {kind} arithmetic {arith}")
         with sf_arithmetic(arith):
             api.sf_apply(Z, U.to(d), V.to(d), -1.0)
             torch.cuda.synchronize()
@@ -103,15 +104,15 @@ def test_sf_half_values_out_of_range_stay_fp32_grade(kind):
     assert units[api.SF_BF16X6] <= 2 * units[api.SF_FP32] + 4, units
 
 
-def test_sf_half_non_finite_operands():
-    """An infinite factor value makes its row of the gradient NaN, as with the
-    products of bf16 parts, and no other."""
+def test_sf_large_non_finite_operands():
+    """An infinite factor value makes its row of the gradient NaN (its bf16
+    parts are infinite and not a number), and no other."""
     d = dev()
     M, N, K = 4133, 4099, 130
     U, V = I.randn(81, (K, M), 1.0), I.randn(82, (K, N), 1.0)
     U[40, 700] = float("inf")
     Z = torch.zeros(M, N, device=d)
-    log("sf half infinite value")
+    log("sf large infinite value")
     api.sf_apply(Z, U.to(d), V.to(d), -1.0)
     torch.cuda.synchronize()
     assert bool(torch.isnan(Z[700]).all())
@@ -129,10 +130,10 @@ def _layers(d, seed, shapes):
     return [(rnd(M, N) * 0.01, rnd(K, M), rnd(K, N)) for M, N, K in shapes]
 
 
-def test_sf_half_scratch_of_streams_and_threads():
-    """Each stream's scratch is its own: layers rebuilt on two streams at once
-    from two threads, on one stream from two threads, and with growing and
-    shrinking operands end as one after the other."""
+def test_sf_large_streams_and_threads():
+    """Layers rebuilt on two streams at once from two threads, on one stream
+    from two threads, and with growing and shrinking operands end as one after
+    the other."""
     d = dev()
     shapes = [(4096, 4096, 128), (4096, 8192, 200), (4096, 4096, 300)]
     want = [_layers(d, 7 + t, shapes) for t in range(4)]
@@ -153,7 +154,7 @@ def test_sf_half_scratch_of_streams_and_threads():
         except Exception as e:   # noqa: BLE001
             failed.append(e)
 
-    log("sf half scratch, four threads on two streams")
+    log("sf large, four threads on two streams")
     threads = [threading.Thread(target=work, args=(t,)) for t in range(4)]
     for t in threads:
         t.start()
@@ -164,7 +165,7 @@ def test_sf_half_scratch_of_streams_and_threads():
     for a, b in zip(want, got):
         for (Wa, _, _), (Wb, _, _) in zip(a, b):
             assert torch.equal(Wa, Wb)
-    # Destroying a pool gives the scratch back; the next rebuild finds some again.
+    # A pool that goes meanwhile takes nothing with it.
     api.StreamPool(1).close()
     Z1, Z2 = torch.zeros(4096, 4096, device=d), torch.zeros(4096, 4096, device=d)
     _, U, V = want[0][0]
@@ -175,13 +176,94 @@ def test_sf_half_scratch_of_streams_and_threads():
     assert torch.equal(Z1, Z2)
 
 
-# Spread rebuilds beside longer applies: 64 x 64 and 128 x 128 tiles cut by the
-# matrix edges and a K that is no multiple of a slice, and the split operands'.
+def test_sf_large_sums_of_one_product():
+    """Outputs made of one nonzero product (one-hot, dropped-out and rectified
+    factors make sums of few) keep the precision of the exact split.
+
+    With bf16 parts h + m + l of both operands, |m| <= 2^-8 and |l| <= 2^-17 of
+    the value's binade, the products left out are below 2 * 2^-25 + 2^-34 of the
+    product.  The six kept are exact; adding them up, the small ones first,
+    rounds at the size of the first five's sums, below 2^-6 of the product (at
+    most four units of 2^-29 of it), and once at the size of the product: a unit
+    of its last place, 2^-23 of it, if the adder truncates."""
+    d = dev()
+    M, N, K = 4096, 4096, 256
+    g = torch.Generator("cuda").manual_seed(92)
+    V = torch.randn(K, N, generator=g, device=d)
+    u = torch.randn(M, generator=g, device=d)
+    k = torch.randint(0, K, (M,), generator=g, device=d)
+    U = torch.zeros(K, M, device=d).scatter_(0, k[None], u[None])
+    Z, b = torch.zeros(M, N, device=d), torch.zeros(M, N, device=d)
+    log("sf large, one product per sum")
+    api.sf_apply_momentum(Z, b, U, V, -1.0, 0.0)
+    torch.cuda.synchronize()
+    assert torch.equal(Z, b)
+    want = u.double()[:, None] * V[k].double()
+    err = float(((b.double() - want) / want).abs().max())
+    assert err <= 2.0 ** -24 + 2.0 ** -34 + 2.0 ** -23 + 4 * 2.0 ** -29, f"{err / 2.0 ** -23} units"
+
+
+def _classifier_factors(d, K, M, N):
+    """A classifier's factors: softmax minus one-hot over the batch, and
+    rectified activations."""
+    g = torch.Generator("cuda").manual_seed(95)
+    rnd = lambda *s: torch.randn(*s, generator=g, device=d)   # noqa: E731
+    U = torch.softmax(rnd(K, M), 1)
+    U[torch.arange(K, device=d), torch.randint(0, M, (K,), generator=g, device=d)] -= 1
+    return U / K, torch.relu(rnd(K, N)), rnd(K, M), rnd(K, N)
+
+
+def test_sf_large_time_does_not_depend_on_the_values():
+    """The rebuild's work is the same for every value, so a classifier's
+    factors take no longer than normal ones (half again allows for the clocks)."""
+    d = dev()
+    M, N, K = 21841, 4096, 512
+    Uc, Vc, Un, Vn = _classifier_factors(d, K, M, N)
+    W = torch.zeros(M, N, device=d)
+    log("sf large, time on two kinds of values")
+    ms = {}
+    for _ in range(5):
+        for kind, U, V in (("normal", Un, Vn), ("classifier", Uc, Vc)):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            api.sf_apply(W, U, V, 1e-6)
+            a.record()
+            for _ in range(5):
+                api.sf_apply(W, U, V, 1e-6)
+            b.record()
+            b.synchronize()
+            ms.setdefault(kind, []).append(a.elapsed_time(b) / 5)
+    assert min(ms["classifier"]) <= 1.5 * min(ms["normal"]), ms
+
+
+def test_sf_large_keeps_no_device_memory():
+    """The library allocates no device memory: none for a large rebuild on
+    streams that it has not seen.  (Small rebuilds first: the runtime's own
+    memory per stream.)"""
+    d = dev()
+    (W, U, V), (w, u, v) = _layers(d, 97, [(4096, 8192, 512), (64, 64, 32)])
+    streams = [torch.cuda.Stream(d) for _ in range(4)]
+    for s in streams:
+        api.sf_apply(w, u, v, 0.01, stream=s)
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info(d)[0]
+    log("sf large, device memory")
+    for s in streams:
+        with torch.cuda.stream(s):
+            api.sf_apply(W, U, V, 0.01)
+            s.synchronize()
+    # The factors of one such layer, split, would be 25 MB a stream.
+    assert before - torch.cuda.mem_get_info(d)[0] < 8 << 20
+
+
+# Spread rebuilds beside longer applies (few workgroups that walk the tiles: at
+# least two tiles each, on no more workgroups than the chip holds at once): 64 x
+# 64 and 128 x 128 tiles cut by the matrix edges and a K that is no multiple of a
+# slice, with a momentum buffer and without.
 @pytest.mark.parametrize("M,N,B,P,n,momentum", [(1000, 2048, 23, 12, 4_400_001, False),
                                                 (1000, 2048, 23, 12, 4_400_001, True),
                                                 (4100, 4000, 9, 4, 8_400_003, False),
                                                 (4096, 4096, 32, 8, 24_000_000, False),
-                                                (4100, 4033, 33, 8, 24_000_000, True)])
+                                                (4100, 4033, 33, 8, 28_000_000, True)])
 def test_sync_iteration_spread_rebuild_equals_the_single_call(M, N, B, P, n, momentum):
     d = dev()
     K = B * P
