@@ -48,15 +48,16 @@ def _dev_f32(name: str, t: torch.Tensor) -> torch.Tensor:
 # handle and the current device -- straight from the runtime's own accessors: a
 # torch.cuda.Stream object and a torch.cuda.device context per call took 2.5 of
 # the 5 us that a KV-store receive costs (sixteen of them and one apply: 84 us,
-# the apply alone 24).
-_raw_stream = torch._C._cuda_getCurrentRawStream
-_current_device = torch._C._cuda_getDevice
+# the apply alone 24).  They are private to torch: where one is missing, its
+# public counterpart serves.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", torch.cuda.current_device)
 _SAME_DEVICE = contextlib.nullcontext()
 
 
 def _stream_handle(stream, device) -> int:
     if stream is None:
-        if device.index is not None:
+        if _raw_stream is not None and device.index is not None:
             return _raw_stream(device.index)
         stream = torch.cuda.current_stream(device)
     return int(stream.cuda_stream) if hasattr(stream, "cuda_stream") else int(stream)
