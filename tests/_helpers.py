@@ -68,6 +68,20 @@ def sample_points(M: int, N: int, count: int, seed: int):
     return np.array(rows, dtype=np.int64), np.array(cols, dtype=np.int64)
 
 
+def kernels(call) -> list:
+    """What `call` launches: the kernels' names with their template arguments,
+    without namespace and parameters.  A test that is about
+    one variant asserts that it ran: which one a call takes is a matter of sizes
+    and of rates that may change."""
+    from torch.profiler import ProfilerActivity, profile
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as p:
+        call()
+        torch.cuda.synchronize()
+    names = [e.name for e in p.events() if e.device_type == torch.autograd.DeviceType.CUDA]
+    return [n.replace("void ", "").replace("poseidon::(anonymous namespace)::", "").split("(")[0] for n in names]
+
+
 @contextlib.contextmanager
 def sf_arithmetic(a: int):
     """Run the block with the SF products formed as `a` (poseidon_sf_set_arithmetic),

@@ -10,7 +10,8 @@ import pytest
 import torch
 
 import oracle
-from _helpers import BUF_TOL, DELTA_TOL, W_TOL, assert_close, dev, log, sample_points, sf_arithmetic, to_np
+from _helpers import (BUF_TOL, DELTA_TOL, W_TOL, assert_close, dev, kernels, log, sample_points, sf_arithmetic,
+                      to_np)
 from paper_1706_03292_amd import api
 from paper_1706_03292_amd import inputs as I
 
@@ -278,8 +279,12 @@ def test_sync_iteration_spread_rebuild_equals_the_single_call(M, N, B, P, n, mom
     log(f"spread rebuild {M}x{N} K={K} beside {n} values at P={P}, momentum={momentum}")
     pool = api.StreamPool(2)
     pool.set_timing(True)
-    schemes = api.SyncIteration(pool, [fc, ps], B, P, 0.01, 0.9)()
+    schemes = []
+    ran = kernels(lambda: schemes.extend(api.SyncIteration(pool, [fc, ps], B, P, 0.01, 0.9)()))
     assert schemes == [api.SFB, api.PS]
+    assert [k for k in ran if k.startswith("sf_")] == [
+        f"sf_apply_walk_kernel<{'64, 64, 32, 32, 32' if M == 1000 else '128, 128, 16, 64, 64'}, true, "
+        f"{'true' if momentum else 'false'}>"]
     assert {r["stream"] for r in pool.launch_times()} == {0, 1}
     if momentum:
         api.sf_apply_momentum(want["W"], want["buf"], want["U"], want["V"], 0.01, 0.9)

@@ -6,7 +6,7 @@ import pytest
 import torch
 
 import oracle
-from _helpers import BUF_TOL, W_TOL, assert_close, dev, log, sample_points, sf_arithmetic, to_np
+from _helpers import BUF_TOL, W_TOL, assert_close, dev, kernels, log, sample_points, sf_arithmetic, to_np
 from paper_1706_03292_amd import api
 from paper_1706_03292_amd import inputs as I
 
@@ -393,7 +393,7 @@ def test_sync_iteration_is_ordered_on_the_callers_stream(cfg, only):
 def test_sync_iteration_spreads_the_rebuilds_beside_longer_applies(case):
     """When the PS applies are the longer kind on two streams, each SFB
     rebuild runs on few workgroups that walk its tiles (the 1000 x 2048
-    classifier at K = 1024 with two Inception-sized conv kernels at P = 32;
+    classifier at K = 1024 with three Inception-sized conv kernels at P = 32;
     a 4096 x 4096 layer at K = 32 with a 4M-value tensor at P = 8, whose
     tiles are 128 x 128).  The walk runs the one-tile kernel's code, so W
     (and buf) are bitwise those of poseidon_sf_apply(_momentum), and of the
@@ -405,7 +405,7 @@ def test_sync_iteration_spreads_the_rebuilds_beside_longer_applies(case):
     if case.endswith("ragged"):      # K not a multiple of the K-slice (an odd slice count), ragged tile edges
         (M, N), B, P, sizes = ((1000, 2048), 7, 3, [5_400_001]) if small else ((4100, 4000), 5, 8, [4_194_303])
     elif small:
-        (M, N), B, P, sizes = (1000, 2048), 32, 32, [2460843, 2786166]
+        (M, N), B, P, sizes = (1000, 2048), 32, 32, [2173509, 2460843, 2786166]
     else:
         (M, N), B, P, sizes = (4096, 4096), 4, 8, [4 << 20]
     assert oracle.best_scheme(True, M, N, B, P) == oracle.SFB
@@ -421,7 +421,11 @@ def test_sync_iteration_spreads_the_rebuilds_beside_longer_applies(case):
     Wc, Uc, Vc = host[-1]["W"].to(d), host[-1]["U"].to(d), host[-1]["V"].to(d)
     log(f"sync_iteration spread rebuild: {case}, FC {M}x{N} K={K}, PS {sizes} at P={P}")
     pool = api.StreamPool(2)
-    schemes = api.SyncIteration(pool, devt, B, P, lr, mu)()
+    schemes = []
+    ran = kernels(lambda: schemes.extend(api.SyncIteration(pool, devt, B, P, lr, mu)()))
+    walk = (f"sf_apply_walk_kernel<{'64, 64, 32, 32, 32' if small else '128, 128, 16, 64, 64'}, true, "
+            f"{'true' if 'buf' in fc else 'false'}>")
+    assert [k for k in ran if k.startswith("sf_")] == [walk]
     if "buf" in fc:
         bc = host[-1]["buf"].to(d)
         api.sf_apply_momentum(Wc, bc, Uc, Vc, lr, mu)
@@ -439,8 +443,7 @@ def test_sync_iteration_spreads_the_rebuilds_beside_longer_applies(case):
     ev = torch.cuda.Event()
     ev.record(cs)
     pool.set_wfbp_policy(api.WFBP_ALL_LAST)
-    api.SyncIteration(pool, held, B, P, lr, mu)(cs, ready=[ev] * len(held))
-    torch.cuda.synchronize()
+    assert walk in kernels(lambda: api.SyncIteration(pool, held, B, P, lr, mu)(cs, ready=[ev] * len(held)))
     for g, h in zip(devt, held):
         assert torch.equal(g["W"], h["W"])
         if "buf" in g:
@@ -492,7 +495,12 @@ def test_sync_iteration_runs_the_applies_beside_longer_rebuilds(P):
     single = [{k: (v.to(d) if isinstance(v, torch.Tensor) else v) for k, v in h.items()} for h in host]
     log(f"sync_iteration applies beside the rebuild: P={P}, K={K}")
     pool = api.StreamPool(2)
-    schemes = api.SyncIteration(pool, devt, B, P, lr, mu)()
+    schemes = []
+    ran = kernels(lambda: schemes.extend(api.SyncIteration(pool, devt, B, P, lr, mu)()))
+    # The rebuild without values of W loaded ahead, the two aligned tensors lean.
+    assert [k for k in ran if k.startswith("sf_")] == ["sf_apply_kernel<128, 128, 16, 64, 64, true, false, 0, false>"]
+    assert sorted(k for k in ran if "lean" in k) == [f"ps_apply_lean_kernel<{P}, false>",
+                                                      f"ps_apply_lean_kernel<{P}, true>"]
     for h in single[:-1]:
         api.ps_apply(h["W"], h["shards"], lr, mu if "buf" in h else 0.0, h.get("buf"))
     api.sf_apply(single[-1]["W"], single[-1]["U"], single[-1]["V"], lr)
