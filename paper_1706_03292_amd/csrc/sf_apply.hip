@@ -99,15 +99,23 @@ struct Small {
     static constexpr int BM = 64, BN = 64, BK = 32, WM = 32, WN = 32;
 };
 constexpr int64_t BIG_TILES_PER_CU = 4, MID_TILES_PER_CU = 2;
-// 64 x 64 tiles of at most this many per CU (two waves per SIMD), given a
-// contraction of at least this depth, take the pipelined split
-// (Direct::mma_piped).  With and without it: at two tiles per CU 1000 x 2048
-// at K = 1024 34.5 against 36.5 us, K = 256 11.3 and 11.3, K = 96 6.8 and 6.8,
-// K = 64 6.0 and 5.9; at one 1000 x 1024 at K = 1024 21.8 and 23.4; at a
-// sixteenth 256 x 256 at K = 128 4.7 and 4.9; at three 1500 x 2048 at K = 512
-// 29.2 and 28.6, at four 2048 x 2048 36.4 and 35.5.
-constexpr int64_t PIPED_TILES_PER_CU = 2;
-constexpr int64_t PIPED_MIN_K = 128;
+// 64 x 64 tiles take the pipelined split (Direct::mma_piped) from this depth
+// on: with at most one tile per CU (one wave per SIMD, which overlaps with
+// nothing else), and with at most two.  Pipelined against plain, the range
+// over layers of so many tiles, W alone and with a momentum buffer: to one
+// tile per CU 3-5% and 2-5% faster at K = 128-192, 7-8% and 4-6% at 256, 11% and
+// 8-10% at 1024 (1000 x 1024 23.4 -> 21.8 us); to two, 5% slower to 1% faster
+// and 6% slower to 0% below K = 384, 1% slower to 2% faster and 1% slower to 1%
+// faster from 384 to 576, 1-4% faster and 0-2% faster from 640 (1000 x 2048 at K
+// = 1024 36.5 -> 34.5 us).  At three 1500 x 2048 at K = 512 took 29.2 against
+// 28.6, at four 2048 x 2048 36.4 against 35.5.
+constexpr int64_t PIPED_MIN_K_ONE = 128, PIPED_MIN_K_TWO = 640;
+
+bool piped_pays(int64_t tiles, int64_t K)
+{
+    const int64_t cus = device_cu_count();
+    return K >= PIPED_MIN_K_TWO ? tiles <= 2 * cus : K >= PIPED_MIN_K_ONE && tiles <= cus;
+}
 
 // Tile rows an XCD's run walks at a time: 8 of 128 rows (the 128 workgroups
 // an XCD runs together then read 8 U and 16 V panels, the fewest for 128 such
@@ -1025,7 +1033,7 @@ hipError_t launch_tiles(float* W, float* buf, const float* U, const float* V, in
             }
         }
         if constexpr (SPLIT && BM == Small::BM) {
-            if (spread_s <= 0.0 && !room && K >= PIPED_MIN_K && t <= PIPED_TILES_PER_CU * device_cu_count()) {
+            if (spread_s <= 0.0 && !room && piped_pays(t, K)) {
                 sf_apply_kernel<BM, BN, BK, WM, WN, SPLIT, MOM, W_PRE, true><<<t, NT, 0, stream>>>(
                     W, U, V, M, N, K, lr, tmi, tni, buf, mu);
                 return hipGetLastError();
