@@ -32,6 +32,8 @@
 // contiguous shards, many such tensors in one launch, and the KV store's
 // pairs (of one or several tensors) with the P workers' updates at separate
 // addresses.
+#include <type_traits>
+
 #include "common.h"
 #include "ps_group.h"
 
@@ -69,7 +71,7 @@ constexpr int64_t PS_MAX_GRID = int64_t{1} << 30;
 // ---------------------------------------------------------------------------
 // One tensor, P contiguous shards.
 // ---------------------------------------------------------------------------
-template <int PT, bool MOM, bool AL, bool CHAIN>
+template <int PT, bool MOM, bool AL, int AT_ONCE>
 __global__ __launch_bounds__(PS_THREADS) void ps_apply_kernel(float* __restrict__ W, const float* __restrict__ G,
                                                               int P, int64_t n, float lr, float mu,
                                                               float* __restrict__ buf)
@@ -77,7 +79,7 @@ __global__ __launch_bounds__(PS_THREADS) void ps_apply_kernel(float* __restrict_
     const Contiguous src{G, n};
     const int64_t stride = static_cast<int64_t>(gridDim.x) * PS_BLOCK_ELEMS;
     for (int64_t e = static_cast<int64_t>(blockIdx.x) * PS_BLOCK_ELEMS + pair_offset(threadIdx.x); e < n; e += stride)
-        apply_pair<PT, MOM, AL, CHAIN>(W, buf, src, P, e, n, lr, mu);
+        apply_pair<PT, MOM, AL, AT_ONCE>(W, buf, src, P, e, n, lr, mu);
 }
 
 // ---------------------------------------------------------------------------
@@ -166,19 +168,25 @@ hipError_t launch_pt(float* W, const float* G, int32_t P, int64_t n, float lr, f
     // One work block per workgroup; the grid-stride loop only matters beyond 2^30 workgroups.
     const int64_t want = (n + PS_BLOCK_ELEMS - 1) / PS_BLOCK_ELEMS;
     const int grid = static_cast<int>(want < PS_MAX_GRID ? want : PS_MAX_GRID);
+    auto launch = [&](auto aligned, auto at_once) {
+        ps_apply_kernel<PT, MOM, decltype(aligned)::value, decltype(at_once)::value>
+            <<<grid, PS_THREADS, 0, stream>>>(W, G, P, n, lr, mu, buf);
+    };
+    constexpr std::integral_constant<int, PS_PAIR_CHUNK> four{};
     if constexpr (PT == 0) {
-        if (ps_chain(P, n)) {
-            if (al)
-                ps_apply_kernel<PT, MOM, true, true><<<grid, PS_THREADS, 0, stream>>>(W, G, P, n, lr, mu, buf);
-            else
-                ps_apply_kernel<PT, MOM, false, true><<<grid, PS_THREADS, 0, stream>>>(W, G, P, n, lr, mu, buf);
-            return hipGetLastError();
-        }
+        constexpr std::integral_constant<int, PS_CHUNK> eight{};
+        constexpr std::integral_constant<int, 0> none{};
+        const int at_once = ps_at_once(P, n, al, MOM, grid, device_cu_count());
+        if (al)
+            at_once == 0 ? launch(std::true_type{}, none)
+            : at_once == PS_PAIR_CHUNK ? launch(std::true_type{}, four) : launch(std::true_type{}, eight);
+        else
+            at_once == 0 ? launch(std::false_type{}, none) : launch(std::false_type{}, eight);
+    } else if (al) {
+        launch(std::true_type{}, four);
+    } else {
+        launch(std::false_type{}, four);
     }
-    if (al)
-        ps_apply_kernel<PT, MOM, true, false><<<grid, PS_THREADS, 0, stream>>>(W, G, P, n, lr, mu, buf);
-    else
-        ps_apply_kernel<PT, MOM, false, false><<<grid, PS_THREADS, 0, stream>>>(W, G, P, n, lr, mu, buf);
     return hipGetLastError();
 }
 

@@ -210,8 +210,8 @@ __device__ inline void apply_group(float* __restrict__ W, float* __restrict__ bu
 // Two groups of one tensor, e and e + PS_PAIR_GAP (64 lanes' groups apart, so
 // that a wave's two accesses to each array read 2 KB in a row instead of
 // 1 KB; the single-tensor launch): when both are whole their loads are issued
-// together, PS_PAIR_CHUNK shards at a time (PS_CHUNK when P is a run-time
-// value); otherwise the two groups are applied one after the other.  Per element the arithmetic and its order
+// together, AT_ONCE shards at a time; otherwise, and with AT_ONCE 0, the two
+// groups are applied one after the other.  Per element the arithmetic and its order
 // are apply_group's, so the results are the same, bitwise.  Single-tensor
 // launches of 2,621,440 values at P = 32 ran at 5.97-6.03 TB/s against
 // 5.49 with one group per thread, 4,194,304 values at P = 8 at 5.43-5.57
@@ -221,31 +221,32 @@ __device__ inline void apply_group(float* __restrict__ W, float* __restrict__ bu
 // another, momentum included: 1,179,648 values at P = 7 10.6 against 12.2 us
 // and at P = 15 17.2 against 18.7, 1,179,649 at P = 12 14.75 against 16.5 and at
 // P = 31 31.0 against 34.7 (4.9 TB/s), 6,000,001 at P = 20 98.9 against 110.4;
-// add_tail with the groups one after the other 1-10% slower.  CHAIN keeps that
-// earlier order (see ps_chain).
+// add_tail with the groups one after the other 1-10% slower.  AT_ONCE 0 keeps
+// that earlier order (see ps_at_once).
 constexpr int64_t PS_PAIR_GAP = 256;
 constexpr int PS_PAIR_CHUNK = 4;
 
-template <int PT, bool MOM, bool AL, bool CHAIN = false, class Src>
+template <int PT, bool MOM, bool AL, int AT_ONCE = PS_PAIR_CHUNK, class Src>
 __device__ inline void apply_pair(float* __restrict__ W, float* __restrict__ buf, const Src& src, int P, int64_t e,
                                   int64_t end, float lr, float mu)
 {
     const int64_t e1 = e + PS_PAIR_GAP;
-    if (!CHAIN && e1 + 3 < end) {
+    if (AT_ONCE > 0 && e1 + 3 < end) {
         const int64_t at[2] = {e, e1};
+        constexpr int N = AT_ONCE > 0 ? AT_ONCE : 1;   // (not reached with 0)
         f4 s[2] = {ld4<AL>(src(0) + e), ld4<AL>(src(0) + e1)};
         if constexpr (PT > 0) {
 #pragma unroll
-            for (int p0 = 1; p0 < PT; p0 += PS_PAIR_CHUNK) {
-                f4 a[PS_PAIR_CHUNK], b[PS_PAIR_CHUNK];
+            for (int p0 = 1; p0 < PT; p0 += N) {
+                f4 a[N], b[N];
 #pragma unroll
-                for (int c = 0; c < PS_PAIR_CHUNK; ++c)
+                for (int c = 0; c < N; ++c)
                     if (p0 + c < PT) {
                         a[c] = ld4<AL>(src(p0 + c) + e);
                         b[c] = ld4<AL>(src(p0 + c) + e1);
                     }
 #pragma unroll
-                for (int c = 0; c < PS_PAIR_CHUNK; ++c)
+                for (int c = 0; c < N; ++c)
                     if (p0 + c < PT) {
                         s[0] += a[c];
                         s[1] += b[c];
@@ -255,15 +256,15 @@ __device__ inline void apply_pair(float* __restrict__ W, float* __restrict__ buf
             }
         } else {
             int p = 1;
-            for (; p + PS_CHUNK <= P; p += PS_CHUNK) {
-                f4 a[PS_CHUNK], b[PS_CHUNK];
+            for (; p + N <= P; p += N) {
+                f4 a[N], b[N];
 #pragma unroll
-                for (int c = 0; c < PS_CHUNK; ++c) {
+                for (int c = 0; c < N; ++c) {
                     a[c] = ld4<AL>(src(p + c) + e);
                     b[c] = ld4<AL>(src(p + c) + e1);
                 }
 #pragma unroll
-                for (int c = 0; c < PS_CHUNK; ++c) {
+                for (int c = 0; c < N; ++c) {
                     s[0] += a[c];
                     s[1] += b[c];
                 }
@@ -286,23 +287,40 @@ __device__ inline void apply_pair(float* __restrict__ W, float* __restrict__ buf
         st4<AL>(W + e1, w1);
         return;
     }
-    apply_group<PT, MOM, AL, CHAIN>(W, buf, src, P, e, end, lr, mu);
+    apply_group<PT, MOM, AL, AT_ONCE == 0>(W, buf, src, P, e, end, lr, mu);
     if (e1 < end)
-        apply_group<PT, MOM, AL, CHAIN>(W, buf, src, P, e1, end, lr, mu);
+        apply_group<PT, MOM, AL, AT_ONCE == 0>(W, buf, src, P, e1, end, lr, mu);
 }
 
-// Whether a single-tensor launch keeps one group and one shard of the tail
-// after another.  Tensors with waves enough to hide that latency gain nothing
-// from more loads in flight, and where most of P is tail lose by them: with
-// momentum, 4,194,304 values at P = 5 24.8 us this way against 25.9, at P = 7
-// 29.6 against 31.6, 3,100,000 at P = 15 39.2 against 40.4, 2,359,296 at P = 6
-// 16.5 against 16.8 (P = 9 at 4,194,304 41.9 against 38.2 and P = 12 48.3 against
-// 46.8: those don't); 1,700,000 at P = 3 10.0 against 9.6, at P = 7 14.5 against
-// 13.7, at P = 15 24.1 against 22.7.
-constexpr int64_t PS_CHAIN_ABOVE = int64_t{1} << 21;
-inline bool ps_chain(int32_t P, int64_t n)
+// The shards of both groups that a single-tensor launch of a run-time P loads
+// together (AT_ONCE); 0 keeps one group and one shard of the tail after
+// another.
+//
+// 0: tensors with waves enough to hide that latency gain nothing from more
+// loads in flight, and where most of P is tail lose by them: with momentum,
+// 4,194,304 values at P = 5 24.8 us this way against 25.9, at P = 7 29.6 against
+// 31.6, 3,100,000 at P = 15 39.2 against 40.4, 2,359,296 at P = 6 16.5 against
+// 16.8 (P = 9 at 4,194,304 41.9 against 38.2 and P = 12 48.3 against 46.8: those
+// don't); 1,700,000 at P = 3 10.0 against 9.6, at P = 7 14.5 against 13.7, at P =
+// 15 24.1 against 22.7.
+//
+// PS_PAIR_CHUNK: aligned tensors of more than one workgroup per CU, and beyond
+// PS_MANY those with a momentum buffer; else PS_CHUNK.  Up to one workgroup per
+// CU a launch is bound by the chain of its loads; beyond, memory serves sixteen
+// reads a thread at once worse than eight, worst where the shards lie a power of
+// two apart.  One group after another, eight at a time, four: with momentum
+// 1,048,576 values at P = 25 19.4, 19.6 and 18.8 us, 2,097,152 at P = 25 47.5,
+// 42.2 and 38.7, 8,388,608 at P = 24 171, 176 and 169; without 600,000 at P = 25
+// 12.9, 14.1 and 13.4, 1,000,000 at P = 24 19.4, 16.5 and 16.1.  300,000 at P = 25:
+// eight 8.0, four 8.6; 4,194,304 at P = 20 without momentum 60.9 against 63.1;
+// 600,000 at P = 7, whose shards are all tail with eight, 5.9 against 6.3;
+// unaligned tensors are 0-4% slower with four.
+constexpr int64_t PS_MANY = int64_t{1} << 21;
+inline int ps_at_once(int32_t P, int64_t n, bool aligned, bool momentum, int64_t workgroups, int64_t cus)
 {
-    return n > PS_CHAIN_ABOVE && (P < 8 || (P > 12 && P < 16));
+    if (n > PS_MANY && (P < 8 || (P > 12 && P < 16)))
+        return 0;
+    return aligned && P > 8 && workgroups > cus && (momentum || n <= PS_MANY) ? PS_PAIR_CHUNK : PS_CHUNK;
 }
 
 }  // namespace poseidon

@@ -4,7 +4,7 @@ thread's two groups together."""
 import pytest
 import torch
 
-from _helpers import dev, log
+from _helpers import dev, kernels, log
 from paper_1706_03292_amd import api
 from paper_1706_03292_amd import inputs as I
 
@@ -51,20 +51,32 @@ def test_ps_runtime_worker_count_is_the_sum_in_order(P):
 
 
 @pytest.mark.parametrize("P", [3, 7, 9, 13, 15, 17])
-@pytest.mark.parametrize("n", [(1 << 21), (1 << 21) + 4, (1 << 21) + 2049])
-def test_ps_runtime_worker_count_large(P, n):
-    """On both sides of the size from which some worker counts keep one shard
-    after another: the batched pass gives the same bits, and the raw sum (W = 0,
-    lr = -1) is the shards' in order."""
+@pytest.mark.parametrize("n", [1 << 19, (1 << 19) + 4, (1 << 19) + 5, (1 << 21), (1 << 21) + 4, (1 << 21) + 2049])
+@pytest.mark.parametrize("mom", [False, True])
+def test_ps_runtime_worker_count_large(P, n, mom):
+    """On both sides of one workgroup (2048 values) per CU, from which on aligned
+    tensors load four shards at a time instead of eight, and of the size from
+    which some worker counts keep one shard after another and the others four
+    with a momentum buffer only: the batched pass gives the same bits, and the
+    raw sum (W = 0, lr = -1, no momentum) is the shards' in order."""
     d = dev()
-    log(f"ps run-time P={P} n={n}")
+    cus = torch.cuda.get_device_properties(d).multi_processor_count
+    many = n > 1 << 21
+    at_once = 4 if n % 4 == 0 and P > 8 and -(-n // 2048) > cus and (mom or not many) else 8
+    if many and (P < 8 or 12 < P < 16):
+        at_once = 0
+    log(f"ps run-time P={P} n={n} momentum={mom}")
     g = torch.Generator("cuda").manual_seed(P + n)
     G = torch.randn(P, n, generator=g, device=d)
-    W, W2 = torch.zeros(n, device=d), torch.zeros(n, device=d)
+    W, W2, b, b2 = (torch.zeros(n, device=d) for _ in range(4))
     s = G[0].clone()
     for p in range(1, P):
         s += G[p]
-    api.ps_apply(W, G, -1.0)
-    api.ps_apply_batch([(W2, G, None)], -1.0)
+    mu = 0.9 if mom else 0.0
+    assert kernels(lambda: api.ps_apply(W, G, -1.0, mu, b if mom else None)) == [
+        f"ps_apply_kernel<0, {'true' if mom else 'false'}, {'true' if n % 4 == 0 else 'false'}, {at_once}>"]
+    api.ps_apply_batch([(W2, G, b2 if mom else None)], -1.0, mu)
     torch.cuda.synchronize()
     assert torch.equal(W, s) and torch.equal(W2, s)
+    if mom:
+        assert torch.equal(b, s) and torch.equal(b2, s)
